@@ -391,9 +391,8 @@ int kpm_reconstruct_sigma(const double* gamma, int32_t M, const double* energies
  * should then be narrower than a few kT).
  * gamma [M][M][2] (re, im) as kpm_moments_cond writes it, energies_ev [K]
  * Fermi energies, sigma [K]; all host (on_device = 0) or all device pointers.
- * Allocates a device workspace of ~16 (Mp^2 + 2 (n_theta + 64) Mp) bytes,
- * Mp = M rounded up to 64, and frees it before returning; synchronises
- * hip_stream.  Errors: KPM_E_INVALID (NULL, M outside [1, 16384], K < 1,
+ * Allocates a device workspace of ~16 M^2 + 4 n_theta M + 900 n_theta bytes and
+ * frees it before returning; synchronises hip_stream.  Errors: KPM_E_INVALID (NULL, M outside [1, 16384], K < 1,
  * e_min >= e_max, eta <= 0, kT < 0, orbitals_per_nm2 <= 0, n_theta outside
  * [0, 2^20]); KPM_E_DEVICE.
  */
@@ -415,9 +414,10 @@ int kpm_reconstruct_sigma_bastin(const double* gamma, int32_t M, const double* e
  * kpm_reconstruct_sigma_bastin.
  * gamma_nm [M][M][2], gamma_n [M][2], omegas_ev [K], sigma [K][2] (re, im);
  * all host (on_device = 0) or all device pointers (the frequencies are copied
- * to the host either way).  Work per frequency: two coefficient tables and
- * one M x M x n_theta contraction.  Allocates and frees a device workspace;
- * synchronises hip_stream.  Errors: KPM_E_INVALID (NULL, M outside
+ * to the host either way).  Work: one M x 4 M x n_theta / 2 real product for all
+ * frequencies and O(M n_theta) per frequency.  Allocates and frees a device
+ * workspace (~32 M^2 bytes, up to 1 GB for blocks of the product and 16 K n_theta
+ * for the frequencies); synchronises hip_stream.  Errors: KPM_E_INVALID (NULL, M outside
  * [1, 16384], K outside [1, 65536], a frequency <= 0, e_min >= e_max,
  * eta <= 0, kT < 0, orbitals_per_nm2 <= 0, n_theta outside [0, 2^20]);
  * KPM_E_DEVICE.
