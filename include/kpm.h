@@ -556,6 +556,16 @@ int kpm_mlp_eval_loss(kpm_mlp_t* mlp, const float* x, const float* target, const
                       int32_t use_bf16, double* loss_dev_out, void* hip_stream);
 
 /*
+ * Released device buffers (of destroyed plans and networks, and the per-call
+ * workspaces) stay with the library as idle blocks for later calls: per device
+ * at most an eighth of its memory, and never more than what is free for others
+ * beside them.  They are given back when an allocation of the library fails (it
+ * is then tried again) and by this call, which may be made at any time; *bytes
+ * (may be NULL) receives their total size.
+ */
+int kpm_release_workspace(int64_t* bytes);
+
+/*
  * HBM bandwidth probe (measurement support for the roofline; not part of the
  * method).  Streams float4 arrays of bytes_per_array bytes with a grid-stride
  * kernel of the given shape: pattern 0 = copy (dst = src), 1 = read-only
@@ -583,9 +593,10 @@ int kpm_bandwidth_probe(int32_t pattern, int64_t bytes_per_array, int32_t iters,
  * injected since the previous call (0 or 1), or KPM_E_INVALID for nth < 0 or
  * an unknown kind.  Calls from every thread take part in the countdown.
  *
- * kpm_debug_live_allocations returns the number of device buffers the
- * library holds at the moment (plans, networks, per-call workspaces), so a
- * test can check that a failed call released everything it allocated.
+ * kpm_debug_live_allocations returns the number of device buffers in use at
+ * the moment (plans, networks, per-call workspaces; not the idle blocks that
+ * kpm_release_workspace gives back), so a test can check that a failed call
+ * released everything it allocated.
  */
 int32_t kpm_debug_inject_failure(int32_t nth, int32_t kind);
 int64_t kpm_debug_live_allocations(void);

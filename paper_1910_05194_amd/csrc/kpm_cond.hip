@@ -69,7 +69,7 @@ static int cond_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double
 
   // Vectors per batch: two [M][n_orb][Rb] blocks must fit in free memory.
   size_t free_b = 0, total_b = 0;
-  KPM_TRY_HIP(hipMemGetInfo(&free_b, &total_b));
+  KPM_TRY_HIP(mem_available(&free_b, &total_b));
   const double per_vec = 2.0 * M * (double)n_orb * 2 * tsize + 2.0 * (double)n_orb * 2 * tsize;
   const double usable = 0.85 * (double)free_b - 4.0e9;   // plan buffers and moment partials
   int rb_max = (int)std::max(0.0, std::floor(usable / per_vec));
@@ -540,7 +540,7 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
   const size_t vec_b = (size_t)n_elems * P->tsize;
   size_t free_b = 0, total_b = 0;
   int st = KPM_OK;
-  hipError_t e = hipMemGetInfo(&free_b, &total_b);
+  hipError_t e = mem_available(&free_b, &total_b);
   // Room in vectors besides the start copy and a scratch vector: the history
   // takes up to a third of it (3 <= B <= 64, no more than M), each energy of a
   // batch two accumulators.

@@ -1125,7 +1125,7 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
     size_t free_b = 0, total_b = 0;
     // Four vectors with 2 GB to spare, or (arena) with a quarter of the arena left for the rest.
     const bool room = P->use_arena ? 4.0 * vec_b <= 0.75 * (double)P->arena_cap
-                                    : hipMemGetInfo(&free_b, &total_b) == hipSuccess && (double)free_b > 4.0 * vec_b + 2.0e9;
+                                    : mem_available(&free_b, &total_b) == hipSuccess && (double)free_b > 4.0 * vec_b + 2.0e9;
     // The sweep kernels address a lattice row with 32-bit offsets.
     bool rows_fit = true;
     for (int l = 0; l < n_lat; ++l)
@@ -1361,7 +1361,7 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
   H2D(P->plat, pl.data(), pl.size() * sizeof(PhaseLat));
   if (!P->use_arena) {
     // The graph-capture stream and the timing events (not in the allocation-free form).
-    if (e == hipSuccess) e = KPM_HIP(hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking));
+    if (e == hipSuccess && P->use_graph) e = KPM_HIP(hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking));
     for (auto& ev : P->ev)
       if (e == hipSuccess) e = KPM_HIP(hipEventCreate(&ev));
   }

@@ -442,7 +442,7 @@ static int evolve_run(const kpm_lattice_t* lat, const kpm_evolve_params_t* p, do
   const int64_t n_orb = P->n_orb;
   const size_t vec_b = (size_t)n_orb * P->Rp * 2 * P->tsize;
   size_t free_b = 0, total_b = 0;
-  hipError_t e = hipMemGetInfo(&free_b, &total_b);
+  hipError_t e = mem_available(&free_b, &total_b);
   // History: up to 32 vectors (no more than M), in the free memory.
   const double room = std::floor((0.85 * (double)free_b - 1.0e9) / (double)vec_b);
   const int B = (int)std::min<double>(std::min(kEvoHist, std::max(3, M)), room);

@@ -32,17 +32,21 @@ inline hipError_t after_call(hipError_t e) { return (e == hipSuccess && fault_du
 // Status of the kernel launches issued since the last check.
 inline hipError_t launch_status() { return after_call(hipGetLastError()); }
 
-// Device allocations of the library: hipMalloc behind the fault countdown,
-// with a count of live allocations (kpm_debug_live_allocations) so that the
-// error-path tests can see every buffer released.
+// Device allocations of the library: the pool of kpm_pool.hip behind the fault
+// countdown, with a count of the buffers in use (kpm_debug_live_allocations) so
+// that the error-path tests can see every buffer released.
 void live_add(int64_t d);
+hipError_t pool_malloc(void** p, size_t bytes);
+hipError_t pool_free(void* p);
+// hipMemGetInfo with the pool's idle blocks on the current device counted as free.
+hipError_t mem_available(size_t* free_bytes, size_t* total_bytes);
 template <typename T>
 inline hipError_t dev_malloc(T** p, size_t bytes) {
   if (fault_due()) {
     *p = nullptr;
     return fault_error();
   }
-  const hipError_t e = hipMalloc(reinterpret_cast<void**>(p), bytes);
+  const hipError_t e = pool_malloc(reinterpret_cast<void**>(p), bytes);
   if (e == hipSuccess) live_add(1);
   else *p = nullptr;
   return e;
@@ -50,7 +54,7 @@ inline hipError_t dev_malloc(T** p, size_t bytes) {
 inline hipError_t dev_free(void* p) {
   if (!p) return hipSuccess;
   live_add(-1);
-  return hipFree(p);
+  return pool_free(p);
 }
 
 #define KPM_TRY_HIP_STATUS_(expr, text)                                                    \

@@ -1,0 +1,199 @@
+// Device memory of the library (host code): hipMalloc behind a bounded pool of
+// idle blocks.
+//
+// The one-shot entry points (Gamma, single-shot conductivity, time evolution,
+// reconstructions, one-shot DOS) allocate their workspace on each call.  Memory
+// that has been written once costs the driver about 23 ms per GB to hand out
+// again: a 512 x 512 spinful Gamma call (17 GB of Chebyshev blocks, 27 ms of
+// kernels) took 0.5 s, a 0.5 GB one (2.6 ms of kernels) 15 ms.  Released blocks
+// are therefore kept for later calls, within these bounds:
+// - per device, idle blocks take at most an eighth of its memory, and a block is
+//   kept only while at least as much as all idle blocks stays free for others;
+//   the oldest go first;
+// - an allocation that fails gives every idle block back and tries once more;
+// - kpm_release_workspace() gives them back on request;
+// - a block serves a request only if it is at most an eighth larger (or 64 KB).
+// A block is handed out again only after its device has been synchronised since
+// its release (hipFree would have waited at the release), so it may be used on
+// any stream, and a call that failed with work in flight may simply release.
+// One mutex covers the bookkeeping; blocks in use by different threads are
+// distinct.
+
+#include "kpm_internal.h"
+
+#include <algorithm>
+#include <list>
+#include <mutex>
+#include <unordered_map>
+
+namespace kpm {
+
+namespace {
+
+struct Block {
+  void* p;
+  size_t cap;
+  int dev;
+  uint64_t freed;   // release count when it became idle
+};
+
+struct Pool {
+  std::mutex mu;
+  std::unordered_map<void*, Block> used;
+  std::list<Block> idle;                        // oldest first
+  uint64_t releases = 0;
+  std::unordered_map<int, uint64_t> synced;     // per device: release count before its last synchronisation
+};
+
+// Never destroyed: objects with static lifetime may still release memory at exit.
+Pool& pool() {
+  static Pool* p = new Pool();
+  return *p;
+}
+
+size_t round_up(size_t bytes) {
+  const size_t g = bytes < (size_t(1) << 20) ? size_t(4) << 10 : size_t(2) << 20;
+  return (std::max<size_t>(bytes, 1) + g - 1) / g * g;
+}
+
+size_t idle_bytes(const Pool& P, int dev) {
+  size_t n = 0;
+  for (const Block& b : P.idle)
+    if (b.dev == dev) n += b.cap;
+  return n;
+}
+
+// Gives back idle blocks of a device, oldest first, until at most keep bytes are left.
+size_t trim(Pool& P, int dev, size_t keep) {
+  size_t have = idle_bytes(P, dev), gone = 0;
+  for (auto it = P.idle.begin(); it != P.idle.end() && have > keep;) {
+    if (it->dev != dev) {
+      ++it;
+      continue;
+    }
+    have -= it->cap;
+    gone += it->cap;
+    (void)hipFree(it->p);
+    it = P.idle.erase(it);
+  }
+  return gone;
+}
+
+}  // namespace
+
+hipError_t pool_malloc(void** out, size_t bytes) {
+  *out = nullptr;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const size_t need = round_up(bytes);
+  try {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    auto best = P.idle.end();
+    for (auto it = P.idle.begin(); it != P.idle.end(); ++it)
+      if (it->dev == dev && it->cap >= need && it->cap - need <= std::max(need / 8, size_t(64) << 10) &&
+          (best == P.idle.end() || it->cap < best->cap))
+        best = it;
+    if (best != P.idle.end()) {
+      uint64_t& synced = P.synced[dev];
+      if (best->freed > synced) {
+        const uint64_t now = P.releases;
+        e = hipDeviceSynchronize();
+        if (e != hipSuccess) return e;
+        synced = now;
+      }
+      P.used.emplace(best->p, *best);
+      *out = best->p;
+      P.idle.erase(best);
+      return hipSuccess;
+    }
+    void* p = nullptr;
+    e = hipMalloc(&p, need);
+    if (e == hipErrorOutOfMemory && trim(P, dev, 0) > 0) {
+      (void)hipGetLastError();
+      e = hipMalloc(&p, need);
+    }
+    if (e != hipSuccess) return e;
+    try {
+      P.used.emplace(p, Block{p, need, dev, 0});
+    } catch (...) {
+      (void)hipFree(p);
+      return hipErrorOutOfMemory;
+    }
+    *out = p;
+    return hipSuccess;
+  } catch (...) {
+    return hipErrorOutOfMemory;
+  }
+}
+
+hipError_t pool_free(void* p) {
+  try {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    auto it = P.used.find(p);
+    if (it == P.used.end()) return hipErrorInvalidValue;
+    Block b = it->second;
+    P.used.erase(it);
+    int cur = 0;
+    size_t free_b = 0, total_b = 0;
+    bool keep = hipGetDevice(&cur) == hipSuccess && cur == b.dev;   // (another device's limits are not at hand)
+    if (keep && b.cap >= (size_t(16) << 20)) {
+      keep = hipMemGetInfo(&free_b, &total_b) == hipSuccess && b.cap <= total_b / 8;
+      if (keep) {
+        const size_t bound = std::min(total_b / 8, free_b);
+        trim(P, b.dev, bound > b.cap ? bound - b.cap : 0);
+        keep = b.cap <= bound;
+      }
+    }
+    if (keep) {
+      b.freed = ++P.releases;
+      try {
+        P.idle.push_back(b);
+        return hipSuccess;
+      } catch (...) {
+      }
+    }
+    return hipFree(p);
+  } catch (...) {
+    return hipErrorOutOfMemory;
+  }
+}
+
+size_t pool_release() {
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  size_t n = 0;
+  for (const Block& b : P.idle) {
+    n += b.cap;
+    (void)hipFree(b.p);
+  }
+  P.idle.clear();
+  return n;
+}
+
+hipError_t mem_available(size_t* free_bytes, size_t* total_bytes) {
+  hipError_t e = hipMemGetInfo(free_bytes, total_bytes);
+  int dev = 0;
+  if (e == hipSuccess) e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  *free_bytes += idle_bytes(P, dev);
+  return hipSuccess;
+}
+
+}  // namespace kpm
+
+extern "C" int kpm_release_workspace(int64_t* bytes) {
+  try {
+    kpm::clear_error();
+    const size_t n = kpm::pool_release();
+    if (bytes) *bytes = (int64_t)n;
+    return KPM_OK;
+  } catch (...) {
+    kpm::set_error("internal error (exception) in kpm_release_workspace");
+    return KPM_E_DEVICE;
+  }
+}

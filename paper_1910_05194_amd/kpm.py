@@ -153,6 +153,7 @@ def _load():
                                         ctypes.c_int32, ctypes.c_char_p, ctypes.POINTER(c_tune), _D, _P]),
         "kpm_bandwidth_probe": (ctypes.c_int, [ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
                                                ctypes.c_int32, ctypes.c_int32, _P, _D, _D]),
+        "kpm_release_workspace": (ctypes.c_int, [ctypes.POINTER(ctypes.c_int64)]),
         "kpm_debug_inject_failure": (ctypes.c_int32, [ctypes.c_int32, ctypes.c_int32]),
         "kpm_debug_live_allocations": (ctypes.c_int64, []),
     }
@@ -184,6 +185,13 @@ def debug_inject_failure(nth: int, kind: int = 0) -> int:
 def debug_live_allocations() -> int:
     """Device buffers the library holds right now (kpm_debug_live_allocations)."""
     return int(LIB.kpm_debug_live_allocations())
+
+
+def release_workspace() -> int:
+    """kpm_release_workspace: give the library's idle device blocks back; returns their bytes."""
+    n = ctypes.c_int64()
+    _check(LIB.kpm_release_workspace(ctypes.byref(n)))
+    return n.value
 
 
 def last_error() -> str:
