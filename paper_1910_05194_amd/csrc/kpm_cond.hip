@@ -188,7 +188,7 @@ static int cond_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double
         e = chain_run(P, C, s, 0, P->Y, P->X, M - 1, Lb, Llo, Mp, 0, 1.0, &g_stats.chain_bytes);
       // R chain from xi again: R_m = h~^b T_m(H~) xi for m = 0 .. M-1 (M levels, each
       // giving the velocity of the level below).
-      if (e == hipSuccess) e = plan_launch_prep(P, s);
+      if (e == hipSuccess) e = plan_launch_prep(P, s, kPrepStart);
       if (e == hipSuccess) e = chain_run(P, C, s, 1, P->X, P->Y, M, Rblk, Rlo, Mp, p->beta, 1.0, &g_stats.chain_bytes);
     }
     // L chain: L_0 = -h~^a xi, L_1 = H~ L_0, L_n = 2 H~ L_{n-1} - L_{n-2}, kept in the
@@ -217,7 +217,7 @@ static int cond_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double
     }
     // R chain: start again from xi; v_0 = xi, v_1 = H~ v_0, v_{m+1} = 2 H~ v_m - v_{m-1}
     // (in place), with R_m = h~^b v_m from the same pass stored K-blocked in Rblk.
-    if (e == hipSuccess && !sweep_chains) e = plan_launch_prep(P, s);
+    if (e == hipSuccess && !sweep_chains) e = plan_launch_prep(P, s, kPrepStart);
     for (int m = 0; m < M && e == hipSuccess && !sweep_chains; ++m) {
       StepLaunch S;
       S.dots = 0;

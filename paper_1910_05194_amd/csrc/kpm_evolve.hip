@@ -267,7 +267,7 @@ static int evolve_plan(const kpm_lattice_t* lat, int R, int precision, hipStream
   tune.use_graph = 0;
   kpm_plan* P = nullptr;
   KPM_TRY(plan_create(lat, 1, &dp, &tune, &P));
-  const hipError_t e = plan_launch_prep(P, s);
+  const hipError_t e = plan_launch_prep(P, s, kPrepModel);
   if (e != hipSuccess) {
     plan_free(P);
     delete P;

@@ -40,13 +40,16 @@ hipError_t pool_malloc(void** p, size_t bytes);
 hipError_t pool_free(void* p);
 // hipMemGetInfo with the pool's idle blocks on the current device counted as free.
 hipError_t mem_available(size_t* free_bytes, size_t* total_bytes);
+// pooled = false: plain hipMalloc, for calls that a program may make while it
+// captures (reusing an idle block may synchronise the device).
 template <typename T>
-inline hipError_t dev_malloc(T** p, size_t bytes) {
+inline hipError_t dev_malloc(T** p, size_t bytes, bool pooled = true) {
   if (fault_due()) {
     *p = nullptr;
     return fault_error();
   }
-  const hipError_t e = pool_malloc(reinterpret_cast<void**>(p), bytes);
+  const hipError_t e = pooled ? pool_malloc(reinterpret_cast<void**>(p), bytes)
+                              : hipMalloc(reinterpret_cast<void**>(p), bytes);
   if (e == hipSuccess) live_add(1);
   else *p = nullptr;
   return e;

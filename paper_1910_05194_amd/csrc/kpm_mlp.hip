@@ -692,15 +692,15 @@ static int mlp_reserve(kpm_mlp* N, int B) {
   // padded to whole 32-column tiles (at least 16 floats a row).
   const int64_t h = (int64_t)B * N->n_hid, o = (int64_t)B * N->n_out, a = (int64_t)B * std::max(N->n_hid, 16);
   const int64_t n_part = std::max<int64_t>(kLossBlocks, ceil_div(B, 32) * ceil_div(N->n_out, 32));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->Z1, h * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->A1, a * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->Z2, h * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->A2, a * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->Y, o * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->dY, o * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->dZ1, h * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->dZ2, h * 4));
-  KPM_TRY_HIP(::kpm::dev_malloc(&N->partial, n_part * (int64_t)sizeof(double)));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->Z1, h * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->A1, a * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->Z2, h * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->A2, a * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->Y, o * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->dY, o * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->dZ1, h * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->dZ2, h * 4, false));
+  KPM_TRY_HIP(::kpm::dev_malloc(&N->partial, n_part * (int64_t)sizeof(double), false));
   N->cap_b = B;
   return KPM_OK;
 }
@@ -889,11 +889,11 @@ int kpm_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n_out, uint64_t seed,
     o += (sz[i] + 63) / 64 * 64;
   }
   N->n_par = o;
-  hipError_t e = ::kpm::dev_malloc(&N->par, o * 4);
-  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->grad, o * 4);
-  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->m, o * 4);
-  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->v, o * 4);
-  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->loss_dev, sizeof(double));
+  hipError_t e = ::kpm::dev_malloc(&N->par, o * 4, false);
+  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->grad, o * 4, false);
+  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->m, o * 4, false);
+  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->v, o * 4, false);
+  if (e == hipSuccess) e = ::kpm::dev_malloc(&N->loss_dev, sizeof(double), false);
   if (e == hipSuccess) {
     const unsigned gb = (unsigned)ceil_div(o, 256);
     hipLaunchKernelGGL(fill_f32, dim3(gb), dim3(256), 0, 0, N->par, o, 0.f);
@@ -1031,10 +1031,10 @@ int kpm_mlp_fit_scaling(kpm_mlp_t* N, const float* x, const float* target, int64
   KPM_CHECK_ARG(N && x && target && n_rows >= 1, "bad arguments");
   hipStream_t s = (hipStream_t)hip_stream;
   // Each buffer on its own, so that a call after a failed allocation completes the set.
-  if (!N->x_shift) KPM_TRY_HIP(::kpm::dev_malloc(&N->x_shift, N->n_in * 4));
-  if (!N->x_scale) KPM_TRY_HIP(::kpm::dev_malloc(&N->x_scale, N->n_in * 4));
-  if (!N->y_shift) KPM_TRY_HIP(::kpm::dev_malloc(&N->y_shift, N->n_out * 4));
-  if (!N->y_scale) KPM_TRY_HIP(::kpm::dev_malloc(&N->y_scale, N->n_out * 4));
+  if (!N->x_shift) KPM_TRY_HIP(::kpm::dev_malloc(&N->x_shift, N->n_in * 4, false));
+  if (!N->x_scale) KPM_TRY_HIP(::kpm::dev_malloc(&N->x_scale, N->n_in * 4, false));
+  if (!N->y_shift) KPM_TRY_HIP(::kpm::dev_malloc(&N->y_shift, N->n_out * 4, false));
+  if (!N->y_scale) KPM_TRY_HIP(::kpm::dev_malloc(&N->y_scale, N->n_out * 4, false));
   hipLaunchKernelGGL(column_stats_kernel, dim3((unsigned)ceil_div(N->n_in, kStatCols)), dim3(1024), 0, s, x, n_rows,
                      N->n_in, N->x_shift, N->x_scale);
   hipLaunchKernelGGL(column_stats_kernel, dim3((unsigned)ceil_div(N->n_out, kStatCols)), dim3(1024), 0, s, target,

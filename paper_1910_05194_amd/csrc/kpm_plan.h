@@ -54,7 +54,9 @@ void chain_plan_free(ChainPlan* C);
 hipError_t chain_run(const kpm_plan* P, const ChainPlan& C, hipStream_t s, int mode, void* v0, void* w0,
                      int n_levels, void* blk, void* blk_lo, int64_t blk_rows, int vdir, double vel_scale,
                      double* bytes);
-hipError_t plan_launch_prep(kpm_plan* P, hipStream_t s);
+// The model (site arrays, Peierls table, active-orbital count) and the start vectors (into X).
+enum { kPrepModel = 1, kPrepStart = 2 };
+hipError_t plan_launch_prep(kpm_plan* P, hipStream_t s, int what = kPrepModel | kPrepStart);
 int plan_set_vector_base(kpm_plan* P, int64_t r0);
 // arena_get != nullptr: after the arguments are validated, arena_get supplies a device arena of
 // arena_cap bytes; every device buffer is carved from it instead of hipMalloc, and no stream, event

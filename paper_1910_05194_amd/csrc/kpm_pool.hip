@@ -133,7 +133,7 @@ hipError_t pool_free(void* p) {
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
     auto it = P.used.find(p);
-    if (it == P.used.end()) return hipErrorInvalidValue;
+    if (it == P.used.end()) return hipFree(p);   // not from the pool
     Block b = it->second;
     P.used.erase(it);
     int cur = 0;
