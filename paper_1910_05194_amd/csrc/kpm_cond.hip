@@ -291,52 +291,108 @@ static int cond_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double
   return st;
 }
 
-// Rank-1 tensor Gamma_n^{ab} = Tr[h~^{ab} T_n(H~)] / (N (1 + d_n0)) (paper eq.
-// Gammanm family, rank 1), h~^{ab} = [r^a, [r^b, H]] Hermitian, with the
-// stochastic trace: (1/(R N)) sum_r <T_n(H~) r | h~^{ab} r>.  u = h~^{ab} r comes
-// from one velocity-only launch of the step kernel (second-order weights);
-// the recursion then runs in place over two buffers and each step's dot
-// product <v_n | u> is summed per workgroup in FP64 and reduced in a fixed
-// order at the end.
 constexpr int kDotBlocks = 1024;
+constexpr int kDotVecs = 8;   // history vectors per pass of the dot products
 
 template <typename T>
-__global__ void dot_partial_kernel(const T* __restrict__ v, const T* __restrict__ u, int64_t n_cplx,
-                                   double* __restrict__ part) {
-  __shared__ double sr[256], si[256];
-  double ar = 0.0, ai = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_cplx; i += (int64_t)gridDim.x * blockDim.x) {
-    const double vr = v[2 * i], vi = v[2 * i + 1], ur = u[2 * i], ui = u[2 * i + 1];
-    ar += vr * ur + vi * ui;   // conj(v) u
-    ai += vr * ui - vi * ur;
+struct DotPtrs {
+  const T* v[kDotVecs];
+};
+
+// <v_b|u> for b < nb <= kDotVecs in one pass over u and the v_b: per-workgroup FP64
+// partial sums part[b][kDotBlocks][2].  One pass per vector read u again each time
+// (7.3 us of every 20 us step at 512^2, 4 vectors).
+template <typename T>
+__global__ void __launch_bounds__(256) dot_partial_kernel(DotPtrs<T> H, int nb, const T* __restrict__ u, int64_t n_packs,
+                                                          double* __restrict__ part) {
+  constexpr int NC = Pack<T>::NC;
+  __shared__ double red[4][2 * kDotVecs];
+  double ar[kDotVecs], ai[kDotVecs];
+#pragma unroll
+  for (int b = 0; b < kDotVecs; ++b) ar[b] = ai[b] = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_packs; i += (int64_t)gridDim.x * 256) {
+    const Pack<T> y = ld_pack(u + i * 2 * NC);
+#pragma unroll
+    for (int b = 0; b < kDotVecs; ++b) {
+      if (b < nb) {
+        const Pack<T> x = ld_pack(H.v[b] + i * 2 * NC);
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+          const double vr = x.v[2 * j], vi = x.v[2 * j + 1], ur = y.v[2 * j], ui = y.v[2 * j + 1];
+          ar[b] = fma(vr, ur, fma(vi, ui, ar[b]));    // conj(v) u
+          ai[b] = fma(vr, ui, fma(-vi, ur, ai[b]));
+        }
+      }
+    }
   }
-  sr[threadIdx.x] = ar;
-  si[threadIdx.x] = ai;
+#pragma unroll
+  for (int b = 0; b < kDotVecs; ++b) {
+    if (b < nb) {
+      double r = ar[b], m = ai[b];
+#pragma unroll
+      for (int x = 1; x < 64; x <<= 1) {
+        r += __shfl_xor(r, x);
+        m += __shfl_xor(m, x);
+      }
+      if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6][2 * b] = r;
+        red[threadIdx.x >> 6][2 * b + 1] = m;
+      }
+    }
+  }
   __syncthreads();
-  for (int st = blockDim.x / 2; st > 0; st >>= 1) {
+  if ((int)threadIdx.x < 2 * nb)
+    part[((int64_t)(threadIdx.x >> 1) * kDotBlocks + blockIdx.x) * 2 + (threadIdx.x & 1)] =
+        (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+}
+
+// (re, im) of the sum of one dot product's partials, on thread 0: one workgroup per product.
+__device__ inline double2 dot_total(const double* part, int64_t n) {
+  __shared__ double sr[256], si[256];
+  double re = 0.0, im = 0.0;
+  for (int b = threadIdx.x; b < kDotBlocks; b += 256) {
+    re += part[(n * kDotBlocks + b) * 2];
+    im += part[(n * kDotBlocks + b) * 2 + 1];
+  }
+  sr[threadIdx.x] = re;
+  si[threadIdx.x] = im;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
     if ((int)threadIdx.x < st) {
       sr[threadIdx.x] += sr[threadIdx.x + st];
       si[threadIdx.x] += si[threadIdx.x + st];
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = sr[0];
-    part[2 * blockIdx.x + 1] = si[0];
-  }
+  return make_double2(sr[0], si[0]);
 }
 
-__global__ void gamma1_finish_kernel(const double* part, int M, int R, const unsigned long long* active, double* out) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= M) return;
-  double re = 0.0, im = 0.0;
-  for (int b = 0; b < kDotBlocks; ++b) {
-    re += part[((int64_t)n * kDotBlocks + b) * 2];
-    im += part[((int64_t)n * kDotBlocks + b) * 2 + 1];
-  }
+template <typename T>
+static hipError_t launch_dots(const void* const* v, int nb, const void* u, int64_t n_packs, double* part, hipStream_t s) {
+  DotPtrs<T> H;
+  for (int b = 0; b < kDotVecs; ++b) H.v[b] = (const T*)v[std::min(b, nb - 1)];
+  hipLaunchKernelGGL(dot_partial_kernel<T>, dim3(kDotBlocks), dim3(256), 0, s, H, nb, (const T*)u, n_packs, part);
+  return ::kpm::launch_status();
+}
+
+// Rank-1 tensor Gamma_n^{ab} = Tr[h~^{ab} T_n(H~)] / (N (1 + d_n0)) (paper eq.
+// Gammanm family, rank 1), h~^{ab} = [r^a, [r^b, H]] Hermitian, with the
+// stochastic trace: (1/(R N)) sum_r <T_n(H~) r | h~^{ab} r>.  u = h~^{ab} r comes
+// from one velocity-only launch of the step kernel (second-order weights).  The
+// recursion writes T_n r into a ring of up to kGamma1Hist vectors (history sweeps
+// on the spinless lattices), and each kDotVecs of them meet u in one pass; without
+// memory for a ring it runs in place over two buffers, one vector per pass.
+constexpr int kGamma1Hist = 8;
+
+__global__ void __launch_bounds__(256) gamma1_finish_kernel(const double* part, int R, const unsigned long long* active,
+                                                            double* out) {
+  const int n = blockIdx.x;
+  const double2 t = dot_total(part, n);
   const double sc = 1.0 / ((double)R * (double)active[0] * (n == 0 ? 2.0 : 1.0));
-  out[2 * n] = re * sc;
-  out[2 * n + 1] = im * sc;
+  if (threadIdx.x == 0) {
+    out[2 * n] = t.x * sc;
+    out[2 * n + 1] = t.y * sc;
+  }
 }
 
 static int gamma1_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double* g1, int32_t on_dev,
@@ -361,23 +417,34 @@ static int gamma1_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, doub
   tune.kernel = 2;
   kpm_plan* P = nullptr;
   KPM_TRY(plan_create(lat, 1, &dp, &tune, &P));
-  const int64_t n_cplx = P->n_orb * P->Rp;
-  void* U = nullptr;
+  const int64_t n_packs = P->n_orb * P->Rp / P->NC;
+  const size_t vec_b = (size_t)P->n_orb * P->Rp * 2 * P->tsize;
+  void *U = nullptr, *hist = nullptr;
   double *part = nullptr, *gdev = nullptr;
+  HistPlan H;
   int st = KPM_OK;
-  hipError_t e = ::kpm::dev_malloc(&U, (size_t)n_cplx * 2 * P->tsize);
+  hipError_t e = ::kpm::dev_malloc(&U, vec_b);
   if (e == hipSuccess) e = ::kpm::dev_malloc(&part, (size_t)M * kDotBlocks * 2 * sizeof(double));
   if (e == hipSuccess && !on_dev) e = ::kpm::dev_malloc(&gdev, (size_t)M * 2 * sizeof(double));
-  if (e == hipSuccess) st = plan_set_vector_base(P, 0);
+  // The ring: T_n r in slot n mod B (n = 0: X itself).  With less room than a sweep
+  // needs beside its two inputs, in place.
+  int B = 0;
+  if (e == hipSuccess) {
+    size_t free_b = 0, total_b = 0;
+    e = mem_available(&free_b, &total_b);
+    B = (int)std::min<double>(std::min(kGamma1Hist, M), std::floor((0.85 * (double)free_b - 1.0e9) / (double)vec_b));
+    if (B < kHistSteps + 2) B = 0;
+    if (e == hipSuccess && B > 0) e = ::kpm::dev_malloc(&hist, vec_b * (size_t)B);
+  }
+  if (e == hipSuccess && B > 0) {
+    st = hist_plan_create(P, &H);
+    if (st == KPM_E_UNSUPPORTED) st = KPM_OK;   // single steps
+  }
+  if (e == hipSuccess && st == KPM_OK) st = plan_set_vector_base(P, 0);
   if (e == hipSuccess && st == KPM_OK) e = plan_launch_prep(P, s);
-  auto dot = [&](const void* v, int n) {
-    if (P->prec == KPM_FP32)
-      hipLaunchKernelGGL(dot_partial_kernel<float>, dim3(kDotBlocks), dim3(256), 0, s, (const float*)v, (const float*)U,
-                         n_cplx, part + (int64_t)n * kDotBlocks * 2);
-    else
-      hipLaunchKernelGGL(dot_partial_kernel<double>, dim3(kDotBlocks), dim3(256), 0, s, (const double*)v,
-                         (const double*)U, n_cplx, part + (int64_t)n * kDotBlocks * 2);
-    return ::kpm::launch_status();
+  auto dots = [&](const void* const* v, int nb, int n0) {
+    double* pn = part + (int64_t)n0 * kDotBlocks * 2;
+    return P->prec == KPM_FP32 ? launch_dots<float>(v, nb, U, n_packs, pn, s) : launch_dots<double>(v, nb, U, n_packs, pn, s);
   };
   if (e == hipSuccess && st == KPM_OK) {
     // u = h~^{ab} xi (velocity-only launch: no output vector, no dots).
@@ -386,27 +453,43 @@ static int gamma1_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, doub
     S.velocity = true; S.vel = U; S.vdir = 2 + p->alpha + p->beta; S.vel_scale = 1.0;
     e = plan_launch_step(P, s, S);
   }
-  void* cur = P->X;
-  void* prev = P->Y;
-  for (int n = 0; n < M && e == hipSuccess && st == KPM_OK; ++n) {
-    if (n == 1) {
-      StepLaunch S;
-      S.v = P->X; S.out = P->Y; S.read_w = 0; S.a = 1.0; S.b = 0.0; S.dots = 0;
-      e = plan_launch_step(P, s, S);
-      cur = P->Y;
-      prev = P->X;
-    } else if (n >= 2) {
-      StepLaunch S;
-      S.v = cur; S.w = prev; S.out = prev; S.dots = 0;   // v_n over v_{n-2}, in place
-      e = plan_launch_step(P, s, S);
-      std::swap(cur, prev);
+  if (B > 0) {
+    const std::function<void*(int)> at = [&](int n) -> void* {
+      return n == 0 ? P->X : (char*)hist + vec_b * (size_t)(n % B);
+    };
+    for (int n0 = 0; n0 < M && e == hipSuccess && st == KPM_OK; n0 += B) {
+      const int n1 = std::min(M, n0 + B);
+      e = history_run(P, &H, s, std::max(1, n0), n1, B - 2, at);
+      for (int n = n0; n < n1 && e == hipSuccess; n += kDotVecs) {
+        const void* v[kDotVecs];
+        const int nb = std::min(kDotVecs, n1 - n);
+        for (int b = 0; b < nb; ++b) v[b] = at(n + b);
+        e = dots(v, nb, n);
+      }
     }
-    if (e == hipSuccess) e = dot(cur, n);
+  } else {
+    void* cur = P->X;
+    void* prev = P->Y;
+    for (int n = 0; n < M && e == hipSuccess && st == KPM_OK; ++n) {
+      if (n == 1) {
+        StepLaunch S;
+        S.v = P->X; S.out = P->Y; S.read_w = 0; S.a = 1.0; S.b = 0.0; S.dots = 0;
+        e = plan_launch_step(P, s, S);
+        cur = P->Y;
+        prev = P->X;
+      } else if (n >= 2) {
+        StepLaunch S;
+        S.v = cur; S.w = prev; S.out = prev; S.dots = 0;   // v_n over v_{n-2}, in place
+        e = plan_launch_step(P, s, S);
+        std::swap(cur, prev);
+      }
+      const void* v = cur;
+      if (e == hipSuccess) e = dots(&v, 1, n);
+    }
   }
   if (e == hipSuccess && st == KPM_OK) {
     double* out = on_dev ? g1 : gdev;
-    hipLaunchKernelGGL(gamma1_finish_kernel, dim3((unsigned)ceil_div(M, 256)), dim3(256), 0, s, part, M, R, P->active,
-                       out);
+    hipLaunchKernelGGL(gamma1_finish_kernel, dim3(M), dim3(256), 0, s, part, R, P->active, out);
     e = ::kpm::launch_status();
     if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(g1, gdev, (size_t)M * 2 * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -417,8 +500,9 @@ static int gamma1_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, doub
     set_error("kpm_moments_gamma1: %s", hipGetErrorString(e));
     st = (e == hipErrorOutOfMemory) ? KPM_E_NOMEM : KPM_E_DEVICE;
   }
-  for (void* ptr : {U, (void*)part, (void*)gdev})
+  for (void* ptr : {U, hist, (void*)part, (void*)gdev})
     if (ptr) (void)::kpm::dev_free(ptr);
+  hist_plan_free(&H);
   plan_free(P);
   delete P;
   return st;
@@ -476,12 +560,9 @@ __global__ void zero_kernel(T* p, int64_t n) {
     p[i] = (T)0;
 }
 
-__global__ void singleshot_finish_kernel(const double* part, int K, double scale, double* sigma) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  double re = 0.0;
-  for (int b = 0; b < kDotBlocks; ++b) re += part[((int64_t)k * kDotBlocks + b) * 2];
-  sigma[k] = scale * re;
+__global__ void __launch_bounds__(256) singleshot_finish_kernel(const double* part, double scale, double* sigma) {
+  const double2 t = dot_total(part, blockIdx.x);
+  if (threadIdx.x == 0) sigma[blockIdx.x] = scale * t.x;
 }
 
 static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, const double* energies_ev, int32_t K,
@@ -554,6 +635,11 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
     delete P;
     return KPM_E_NOMEM;
   }
+  HistPlan H4;
+  if (e == hipSuccess) {
+    st = hist_plan_create(P, &H4);
+    if (st == KPM_E_UNSUPPORTED) st = KPM_OK;   // single steps
+  }
   void *V0 = nullptr, *Sc = nullptr, *acc = nullptr, *hist = nullptr;
   double *dcoef = nullptr, *part = nullptr, *dsig = nullptr;
   if (e == hipSuccess) e = ::kpm::dev_malloc(&V0, vec_b);
@@ -564,7 +650,7 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
   if (e == hipSuccess) e = ::kpm::dev_malloc(&part, sizeof(double) * 2 * kDotBlocks * (size_t)K);
   if (e == hipSuccess) e = ::kpm::dev_malloc(&dsig, sizeof(double) * K);
   if (e == hipSuccess) e = hipMemcpyAsync(dcoef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) st = plan_set_vector_base(P, 0);
+  if (e == hipSuccess && st == KPM_OK) st = plan_set_vector_base(P, 0);
   const bool f32 = P->prec == KPM_FP32;
   const dim3 eg(2048), eb(256);
   // T_n x0: x0 itself for n = 0, history slot n mod B otherwise.
@@ -595,24 +681,12 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
   // rewritten only after its vector has been flushed).
   auto chain = [&](void* x0, void* A, int k0, int kk) {
     hipError_t er = hipSuccess;
-    int n0 = 0;   // first step not yet flushed
-    for (int n = 1; n < M && er == hipSuccess; ++n) {
-      StepLaunch S;
-      S.dots = 0;
-      S.v = hvec(x0, n - 1);
-      S.out = hvec(x0, n);
-      if (n == 1) {
-        S.read_w = 0; S.a = 1.0; S.b = 0.0;
-      } else {
-        S.w = hvec(x0, n - 2);
-      }
-      er = plan_launch_step(P, s, S);
-      if (er == hipSuccess && n + 1 - n0 == B) {
-        er = flush(x0, A, n0, B, k0, kk);
-        n0 = n + 1;
-      }
+    const std::function<void*(int)> at = [&](int n) { return hvec(x0, n); };
+    for (int n0 = 0; n0 < M && er == hipSuccess; n0 += B) {
+      const int n1 = std::min(M, n0 + B);
+      er = history_run(P, &H4, s, std::max(1, n0), n1, B - 2, at);
+      if (er == hipSuccess) er = flush(x0, A, n0, n1 - n0, k0, kk);
     }
-    if (er == hipSuccess && n0 < M) er = flush(x0, A, n0, M - n0, k0, kk);
     return er;
   };
   for (int k0 = 0; k0 < K && e == hipSuccess && st == KPM_OK; k0 += kb) {
@@ -641,20 +715,15 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
       e = plan_launch_step(P, s, S);
       if (e != hipSuccess) break;
       double* pk = part + (size_t)(k0 + k) * kDotBlocks * 2;
-      if (f32)
-        hipLaunchKernelGGL(dot_partial_kernel<float>, dim3(kDotBlocks), dim3(256), 0, s,
-                           (const float*)(Ab + vec_b * (size_t)k), (const float*)Sc, n_elems / 2, pk);
-      else
-        hipLaunchKernelGGL(dot_partial_kernel<double>, dim3(kDotBlocks), dim3(256), 0, s,
-                           (const double*)(Ab + vec_b * (size_t)k), (const double*)Sc, n_elems / 2, pk);
-      e = ::kpm::launch_status();
+      const void* ak = Ab + vec_b * (size_t)k;
+      const int64_t n_packs = n_elems / (2 * P->NC);
+      e = f32 ? launch_dots<float>(&ak, 1, Sc, n_packs, pk, s) : launch_dots<double>(&ak, 1, Sc, n_packs, pk, s);
     }
   }
   if (e == hipSuccess && st == KPM_OK) {
     const double omega = (double)lat->L1 * lat->L2 * cell_area_nm2(lat->kind);
     double* out = on_dev ? sigma : dsig;
-    hipLaunchKernelGGL(singleshot_finish_kernel, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, s, part, K,
-                       2.0 * M_PI * M_PI / (omega * R), out);
+    hipLaunchKernelGGL(singleshot_finish_kernel, dim3(K), dim3(256), 0, s, part, 2.0 * M_PI * M_PI / (omega * R), out);
     e = ::kpm::launch_status();
     if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(sigma, dsig, sizeof(double) * K, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -667,6 +736,7 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
   }
   for (void* ptr : {V0, Sc, acc, hist, (void*)dcoef, (void*)part, (void*)dsig})
     if (ptr) (void)::kpm::dev_free(ptr);
+  hist_plan_free(&H4);
   plan_free(P);
   delete P;
   return st;

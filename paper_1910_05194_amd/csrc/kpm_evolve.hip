@@ -339,7 +339,7 @@ static int wavepacket_run(const kpm_lattice_t* lat, int32_t n_k, const double* k
 
 template <typename T>
 static hipError_t evolve_loop(kpm_plan* P, const kpm_evolve_params_t* p, const CellGeom& g, const double2* dcoef,
-                              int B, void* hist, double* part, double* obs, hipStream_t s) {
+                              const HistPlan& H4, int B, void* hist, double* part, double* obs, hipStream_t s) {
   const int M = p->num_moments, R = p->num_packets;
   const int64_t n_cplx = P->n_orb * P->Rp;
   const size_t vec_b = (size_t)n_cplx * 2 * sizeof(T);
@@ -367,32 +367,21 @@ static hipError_t evolve_loop(kpm_plan* P, const kpm_evolve_params_t* p, const C
   if (e == hipSuccess) e = hipEventCreate(&ev1);
   if (e == hipSuccess) e = hipEventRecord(ev0, s);
   if (e == hipSuccess) e = observe(0);
-  // Algorithmic bytes: a recursion step reads v_n (neighbours from cache) and
-  // v_(n-1), writes v_(n+1), reads the per-site arrays; a flush reads its
+  // Algorithmic bytes: a single step reads v_n (neighbours from cache) and
+  // v_(n-1), writes v_(n+1), reads the per-site arrays, a history sweep of up to
+  // kHistSteps steps the same with one vector written per step; a flush reads its
   // history vectors and writes psi(t + dt) (reading it too after the first).
   const double site_b = (double)n_sites * ((P->has_onsite ? (double)sizeof(T) : 0.0) + (P->has_mask ? 1.0 : 0.0));
   const int n_flush = (M + B - 1) / B;
-  const double step_b = (double)(M - 1) * (3.0 * (double)vec_b + site_b) + ((double)M + 2.0 * n_flush - 1.0) * (double)vec_b;
+  const double launches = H4.fn ? (double)ceil_div(M - 1, kHistSteps) : (double)(M - 1);
+  const double step_b = launches * (2.0 * (double)vec_b + site_b) + (double)(M - 1) * (double)vec_b + ((double)M + 2.0 * n_flush - 1.0) * (double)vec_b;
   for (int k = 1; k < p->num_points && e == hipSuccess; ++k) {
-    int n0 = 0, first = 1;
-    for (int n = 1; n < M && e == hipSuccess; ++n) {
-      StepLaunch S;
-      S.dots = 0;
-      S.v = hvec(n - 1);
-      S.out = hvec(n);
-      if (n == 1) {
-        S.read_w = 0; S.a = 1.0; S.b = 0.0;
-      } else {
-        S.w = hvec(n - 2);
-      }
-      e = plan_launch_step(P, s, S);
-      if (e == hipSuccess && n + 1 - n0 == B) {
-        e = flush(n0, B, first);
-        first = 0;
-        n0 = n + 1;
-      }
+    const std::function<void*(int)> at = hvec;
+    for (int n0 = 0; n0 < M && e == hipSuccess; n0 += B) {
+      const int n1 = std::min(M, n0 + B);
+      e = history_run(P, &H4, s, std::max(1, n0), n1, B - 2, at);
+      if (e == hipSuccess) e = flush(n0, n1 - n0, n0 == 0 ? 1 : 0);
     }
-    if (e == hipSuccess && n0 < M) e = flush(n0, M - n0, first);
     std::swap(psi, nxt);
     if (e == hipSuccess) e = observe(k);
   }
@@ -454,6 +443,17 @@ static int evolve_run(const kpm_lattice_t* lat, const kpm_evolve_params_t* p, do
   }
   const size_t n_psi = (size_t)R * n_orb * 2, n_obs = (size_t)p->num_points * R * 8;
   void* hist = nullptr;
+  HistPlan H4;
+  int st = KPM_OK;
+  if (e == hipSuccess) {
+    st = hist_plan_create(P, &H4);
+    if (st == KPM_E_UNSUPPORTED) st = KPM_OK;   // single steps
+    if (st != KPM_OK) {
+      plan_free(P);
+      delete P;
+      return st;
+    }
+  }
   double2* dcoef = nullptr;
   double *part = nullptr, *dpsi = nullptr, *dobs = nullptr;
   if (e == hipSuccess) e = ::kpm::dev_malloc(&hist, vec_b * (size_t)B);
@@ -472,7 +472,7 @@ static int evolve_run(const kpm_lattice_t* lat, const kpm_evolve_params_t* p, do
       hipLaunchKernelGGL(evolve_copy_in_kernel<float>, dim3(gi), dim3(256), 0, s, sp, n_orb, R, P->Rp, g.n_spin,
                          (const uint8_t*)P->mask, (float*)P->X);
       e = ::kpm::launch_status();
-      if (e == hipSuccess) e = evolve_loop<float>(P, p, g, dcoef, B, hist, part, so, s);
+      if (e == hipSuccess) e = evolve_loop<float>(P, p, g, dcoef, H4, B, hist, part, so, s);
       if (e == hipSuccess)
         hipLaunchKernelGGL(evolve_copy_out_kernel<float>, dim3(go), dim3(256), 0, s, (const float*)P->X, n_orb, R,
                            P->Rp, sp);
@@ -480,7 +480,7 @@ static int evolve_run(const kpm_lattice_t* lat, const kpm_evolve_params_t* p, do
       hipLaunchKernelGGL(evolve_copy_in_kernel<double>, dim3(gi), dim3(256), 0, s, sp, n_orb, R, P->Rp, g.n_spin,
                          (const uint8_t*)P->mask, (double*)P->X);
       e = ::kpm::launch_status();
-      if (e == hipSuccess) e = evolve_loop<double>(P, p, g, dcoef, B, hist, part, so, s);
+      if (e == hipSuccess) e = evolve_loop<double>(P, p, g, dcoef, H4, B, hist, part, so, s);
       if (e == hipSuccess)
         hipLaunchKernelGGL(evolve_copy_out_kernel<double>, dim3(go), dim3(256), 0, s, (const double*)P->X, n_orb, R,
                            P->Rp, sp);
@@ -491,13 +491,13 @@ static int evolve_run(const kpm_lattice_t* lat, const kpm_evolve_params_t* p, do
   if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(observables, dobs, sizeof(double) * n_obs, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   else (void)hipStreamSynchronize(s);
-  int st = KPM_OK;
   if (e != hipSuccess) {
     set_error("kpm_time_evolve: %s", hipGetErrorString(e));
     st = (e == hipErrorOutOfMemory) ? KPM_E_NOMEM : KPM_E_DEVICE;
   }
   for (void* ptr : {hist, (void*)dcoef, (void*)part, (void*)dpsi, (void*)dobs})
     if (ptr) (void)::kpm::dev_free(ptr);
+  hist_plan_free(&H4);
   plan_free(P);
   delete P;
   return st;

@@ -3,6 +3,7 @@
 
 #include "kpm_internal.h"
 
+#include <functional>
 #include <vector>
 
 namespace kpm {
@@ -54,6 +55,20 @@ void chain_plan_free(ChainPlan* C);
 hipError_t chain_run(const kpm_plan* P, const ChainPlan& C, hipStream_t s, int mode, void* v0, void* w0,
                      int n_levels, void* blk, void* blk_lo, int64_t blk_rows, int vdir, double vel_scale,
                      double* bytes);
+// History sweeps (kpm_sweep.hip, spinless lattices): up to kHistSteps recursion
+// steps per launch, every T_n x written to a buffer of its own.
+// The step kernels' single steps serve where it has no shape (fn == nullptr).
+struct HistPlan {
+  int block = 0, Tx = 0, Ty = 0, Ew = 0, grid = 0, n_tiles = 0;
+  size_t lds_bytes = 0;
+  int4* tiles = nullptr;
+  void* fn = nullptr;
+};
+// KPM_E_UNSUPPORTED (spinful lattice, no tile shape fits): the caller runs single steps.
+int hist_plan_create(const kpm_plan* P, HistPlan* H);
+void hist_plan_free(HistPlan* H);
+hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, int n1, int max_levels,
+                       const std::function<void*(int)>& at);
 // The model (site arrays, Peierls table, active-orbital count) and the start vectors (into X).
 enum { kPrepModel = 1, kPrepStart = 2 };
 hipError_t plan_launch_prep(kpm_plan* P, hipStream_t s, int what = kPrepModel | kPrepStart);

@@ -141,6 +141,7 @@ struct SweepArgs {
   T a1, b1;
   int read_w1, nlev;
   int Tx, Ty, E, Ew, Rp;            // Tx = thread columns (interior + 2 (KS - 1))
+  T* hist[kHistSteps];              // history sweeps: the buffers of levels 1 .. nlev
 };
 
 // The sweep kernel instance for a precision (KPM_FP32 / KPM_FP64), lattice kind,

@@ -43,7 +43,9 @@ namespace kpm {
 // are discarded once per tile.  With PHASE the neighbour k enters with the
 // complex coefficient (hre[k], him[k]) = hop exp(i theta_k) of the site's
 // column, else with hop.
-template <typename T, int KIND, bool PHASE>
+// HIST: no products, and with PHASE each neighbour's term is rounded before it
+// is added (the single-step kernels' arithmetic, to the bit).
+template <typename T, int KIND, bool PHASE, bool HIST>
 __device__ inline void sweep_site(T a, T b, bool read_w, T hop, const T* hre, const T* him, T ons, bool alive,
                                   const Pack<T>& vo, const Pack<T>& wo, const Pack<T> (&vn)[KindTraits<KIND>::NNB],
                                   Pack<T>& out, bool acc, double* pv, double* pw) {
@@ -54,7 +56,12 @@ __device__ inline void sweep_site(T a, T b, bool read_w, T hop, const T* hre, co
     T hr = ons * vo.v[2 * j], hi = ons * vo.v[2 * j + 1];
 #pragma unroll
     for (int k = 0; k < NNB; ++k) {
-      if constexpr (PHASE) {
+      if constexpr (PHASE && HIST) {
+        T tr = 0, ti = 0;
+        cmul_acc(tr, ti, hre[k], him[k], vn[k].v[2 * j], vn[k].v[2 * j + 1]);
+        hr += tr;
+        hi += ti;
+      } else if constexpr (PHASE) {
         cmul_acc(hr, hi, hre[k], him[k], vn[k].v[2 * j], vn[k].v[2 * j + 1]);
       } else {
         hr += hop * vn[k].v[2 * j];
@@ -74,7 +81,7 @@ __device__ inline void sweep_site(T a, T b, bool read_w, T hop, const T* hre, co
     out.v[2 * j + 1] = oi;
   }
   // One uniform branch for all of the site's products.
-  if (acc) {
+  if (!HIST && acc) {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       const double xr = vo.v[2 * j], xi = vo.v[2 * j + 1];
@@ -88,7 +95,13 @@ __device__ inline void sweep_site(T a, T b, bool read_w, T hop, const T* hre, co
 // the arguments.  SHAPE 1: 512 threads, 8 chunks per site (the shape the
 // benchmarked workloads run): compile-time constants, so every LDS ring
 // offset is an instruction immediate instead of an address register.
-template <typename T, int KIND, bool ONSITE, bool MASK, bool PHASE, int KS, int SHAPE = 0>
+// HIST: a history sweep.  Every level goes to HBM, into a buffer of its own (the
+// callers need each T_n x, not only the last two), and no products are formed.
+// Per KS steps two vectors come in and KS go out, against two in and one out per
+// single step.  Graphene 512^2, 4 vectors, FP32 (16.8 MB a vector): 12.7 us a step
+// single, 30.8 us per sweep of four = 7.7 us a step (3.3 TB/s; the rows are LDS- and
+// VALU-bound: 512 x 2048 takes 26.5 us a step, 3.8 TB/s).
+template <typename T, int KIND, bool ONSITE, bool MASK, bool PHASE, int KS, int SHAPE = 0, bool HIST = false>
 __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
   using P = Pack<T>;
   constexpr int NC = P::NC;
@@ -106,8 +119,9 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
   constexpr int kPrefetch = 1;
   constexpr int kSets = 2;
   constexpr int kLoads = 3 + (ONSITE ? 1 : 0) + (MASK ? 1 : 0);
-  constexpr int kWaitVm = 2 + (kPrefetch - 1) * (kLoads + 2);
-  static_assert(kPrefetch < kSets && 4 % kSets == 0 && kWaitVm < 16, "register sets and wait count");
+  constexpr int kStores = HIST ? KS : 2;
+  constexpr int kWaitVm = kStores + (kPrefetch - 1) * (kLoads + kStores);
+  static_assert(kPrefetch < kSets && 4 % kSets == 0 && kWaitVm < 64, "register sets and wait count");
   extern __shared__ double lds[];
 
   const int tid = threadIdx.x;
@@ -158,6 +172,7 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
   // The two levels that go to HBM (levels nlev - 1 and nlev), kept from the
   // level loop until the row's two stores.
   P o_a = {}, o_b = {};
+  P o_h[HIST ? KS : 1] = {};   // history sweep: all levels
 
   for (int ti = t_begin + jx; ti < t_end; ti += gx) {
     const int4 tl = A.tiles[ti];
@@ -192,8 +207,8 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
     const int64_t coff = (int64_t)c * NC * 2;
     const T* __restrict__ vb = A.v + Lg.vec_off;
     const T* __restrict__ wb = A.w + Lg.vec_off;
-    T* __restrict__ oa = A.out_a + Lg.vec_off;
-    T* __restrict__ ob = A.out_b + Lg.vec_off;
+    T* __restrict__ oa = HIST ? nullptr : A.out_a + Lg.vec_off;
+    T* __restrict__ ob = HIST ? nullptr : A.out_b + Lg.vec_off;
     // Halo cells of v_n: left of thread column 0, right of thread column wcols - 1.
     const int hl = (xe == 0) ? L1 - 1 : xe - 1;
     const int hr = (xe + wcols) % L1;
@@ -300,6 +315,11 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
     // stored to out_a).
     int yf = wrap(y0 + j0 + kPrefetch), ys = wrap(y0 + j0 + kPrefetch - 1), yb = wrap(y0 + j0 - (2 * nlev - 1)),
         ya = wrap(y0 + j0 - (2 * nlev - 3));
+    int yh[HIST ? KS : 1];   // history sweep: the row each level forms
+    if constexpr (HIST) {
+#pragma unroll
+      for (int l = 0; l < KS; ++l) yh[l] = wrap(y0 + j0 - (2 * l + 1));
+    }
     // One iteration with phase p = (j - j0) mod 4: set[p % kSets] holds v_n
     // row y0 + j and the site data of row y0 + j - 1.  v_n row y0 + j sits in
     // LDS slot (p + 2) & 3, the rows level l forms at iteration j in slot p.
@@ -314,7 +334,7 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
       // cur has arrived: everything issued before the last kPrefetch rows'
       // stores and the loads between them is complete (expcnt and lgkmcnt
       // left at their maxima).
-      __builtin_amdgcn_s_waitcnt(0x0F70 | kWaitVm);
+      __builtin_amdgcn_s_waitcnt(0x0F70 | (kWaitVm & 15) | ((kWaitVm >> 4) << 14));
       store_row(cur, (p + 2) & 3);
 #pragma unroll
       for (int k = NH - 1; k > 0; --k) {
@@ -354,16 +374,17 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
           // or level lev-2's output of four iterations back.
           const P wo = (lev == 2) ? r0((p + 3) & 3, x, s) : rl(lev >= 3 ? lev - 2 : 1, p, x, s);
           P o;
-          sweep_site<T, KIND, PHASE>((T)2, (T)1, true, hop, hre, him, ons_h[2 * lev - 2], alive_h[2 * lev - 2], vo, wo,
+          sweep_site<T, KIND, PHASE, HIST>((T)2, (T)1, true, hop, hre, him, ons_h[2 * lev - 2], alive_h[2 * lev - 2], vo, wo,
                                      vn, o, (uint32_t)(j - (2 * lev - 1)) < (uint32_t)ty, tv[lev - 1], tw[lev - 1]);
           if (lev < KS) rl(lev, p, x, s) = o;
           // The stored levels: KS and KS - 1 in a full sweep, else nlev and
           // nlev - 1 of the recursion's last, short sweep (element-wise
           // selects: a conditional copy of the whole pack would be kept in
           // scratch memory).
+          if constexpr (HIST) o_h[lev - 1] = o;
           if (lev == KS) o_b = o;
           if (lev == KS - 1) o_a = o;
-          if (!FULL && nl < KS) {
+          if (!HIST && !FULL && nl < KS) {
             const bool cb = lev == nl, ca = lev == nl - 1;
 #pragma unroll
             for (int q = 0; q < 2 * NC; ++q) {
@@ -395,11 +416,12 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
           }
           const P vo = r0(s0, x, s);   // v_n row y
           P o;
-          sweep_site<T, KIND, PHASE>(A.a1, A.b1, A.read_w1 != 0, hop, hre, him, ons_h[0], alive_h[0], vo, cur.w, vn, o,
+          sweep_site<T, KIND, PHASE, HIST>(A.a1, A.b1, A.read_w1 != 0, hop, hre, him, ons_h[0], alive_h[0], vo, cur.w, vn, o,
                                      (uint32_t)(j - 1) < (uint32_t)ty, tv[0], tw[0]);
           rl(1, p, x, s) = o;
+          if constexpr (HIST) o_h[0] = o;
           if constexpr (KS == 2) o_a = o;   // a full two-step sweep stores levels 1 and 2
-          if (!FULL && nl <= 2) {
+          if (!HIST && !FULL && nl <= 2) {
             const bool cb = nl == 1;
 #pragma unroll
             for (int q = 0; q < 2 * NC; ++q) {
@@ -412,7 +434,16 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
       // The row's two stores: level nlev at row y0 + j - (2 nlev - 1), level
       // nlev - 1 two rows higher (a thread stores its interior cells of the
       // tile's own rows; every other store is dropped).
-      {
+      if constexpr (HIST) {
+        // Level l + 1 at row y0 + j - (2 l + 1).
+#pragma unroll
+        for (int l = 0; l < KS; ++l) {
+          const bool own = inner && l < nl && (uint32_t)(j - (2 * l + 1)) < (uint32_t)ty;
+          T* __restrict__ base = A.hist[l < nl ? l : 0] + Lg.vec_off;
+          buf_st_pack<T>(row_rsrc(row_ptr(base, yh[l], row_bytes), row_bytes), own ? lane_b : kOOB, o_h[l]);
+          yh[l] = next_row(yh[l]);
+        }
+      } else {
         const bool own_b = inner && (uint32_t)(j - (2 * nl - 1)) < (uint32_t)ty;
         const bool own_a = inner && (uint32_t)(j - (2 * nl - 3)) < (FULL ? (uint32_t)ty : a_cnt);
         buf_st_pack<T>(row_rsrc(row_ptr(ob, yb, row_bytes), row_bytes), own_b ? lane_b : kOOB, o_b);
@@ -436,9 +467,14 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
 #pragma unroll
     for (int k = 0; k < kPrefetch; ++k) {
       fetch(set[k], wrap(y0 + j0 + k), wrap(y0 + j0 + k - 1), true);
-      const __amdgpu_buffer_rsrc_t rz = row_rsrc(ob, row_bytes);
-      buf_st_pack<T>(rz, kOOB, o_b);
-      buf_st_pack<T>(rz, kOOB, o_a);
+      const __amdgpu_buffer_rsrc_t rz = row_rsrc(HIST ? A.hist[0] : ob, row_bytes);
+      if constexpr (HIST) {
+#pragma unroll
+        for (int l = 0; l < KS; ++l) buf_st_pack<T>(rz, kOOB, o_h[l]);
+      } else {
+        buf_st_pack<T>(rz, kOOB, o_b);
+        buf_st_pack<T>(rz, kOOB, o_a);
+      }
     }
     auto march = [&](auto full) {
       for (int j = j0; j <= j_last; j += 4) {
@@ -455,6 +491,10 @@ __global__ void __launch_bounds__(kMaxStepBlock) sweep_kernel(SweepArgs<T> A) {
       march(std::true_type{});
     else
       march(std::false_type{});
+    if constexpr (HIST) {
+      __syncthreads();   // the next tile reuses the LDS
+      continue;
+    }
     // The tile's sums count for interior threads only (a select: the others' may be NaN).
 #pragma unroll
     for (int l = 0; l < KS; ++l)
@@ -501,11 +541,172 @@ static void* pick_sweep_kind(int kind, int ks, bool onsite, bool mask, bool phas
                : pick_sweep<T, KPM_HONEYCOMB, false>(ks, onsite, mask, shape1);
 }
 
+template <typename T, int KIND, bool PHASE>
+static void* pick_history(bool onsite, bool mask) {
+  if (onsite)
+    return mask ? (void*)sweep_kernel<T, KIND, true, true, PHASE, kHistSteps, 0, true>
+                : (void*)sweep_kernel<T, KIND, true, false, PHASE, kHistSteps, 0, true>;
+  return mask ? (void*)sweep_kernel<T, KIND, false, true, PHASE, kHistSteps, 0, true>
+              : (void*)sweep_kernel<T, KIND, false, false, PHASE, kHistSteps, 0, true>;
+}
+template <typename T>
+static void* pick_history_kind(int kind, bool onsite, bool mask, bool phase) {
+  if (kind == KPM_SQUARE) return pick_history<T, KPM_SQUARE, false>(onsite, mask);
+  return phase ? pick_history<T, KPM_HONEYCOMB, true>(onsite, mask) : pick_history<T, KPM_HONEYCOMB, false>(onsite, mask);
+}
+
 void* sweep_kernel_fn(int prec, int kind, int ks, bool onsite, bool mask, bool phase, int block, int tx, int ew) {
   const int nsub = kind == KPM_SQUARE ? 1 : 2;
   const bool shape1 = block == 512 && ew == 8 && tx == 512 / (nsub * 8);
   return prec == KPM_FP32 ? pick_sweep_kind<float>(kind, ks, onsite, mask, phase, shape1)
                           : pick_sweep_kind<double>(kind, ks, onsite, mask, phase, shape1);
+}
+
+}  // namespace kpm
+
+// ---------------------------------------------------------------------------
+// History sweeps: launch shape, tile list, launches.
+// ---------------------------------------------------------------------------
+#include "kpm_plan.h"
+
+#include <algorithm>
+#include <functional>
+
+namespace kpm {
+
+int hist_plan_create(const kpm_plan* P, HistPlan* H) {
+  *H = HistPlan();
+  if (P->n_spin != 1 || P->n_lat != 1) return KPM_E_UNSUPPORTED;
+  int dev = 0, lds_max = 65536, n_cu = 256, v = 0;
+  if (hipGetDevice(&dev) == hipSuccess) {
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0) lds_max = v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) n_cu = v;
+  }
+  const kpm_lattice_t& L = P->lats[0];
+  constexpr int ks = kHistSteps;
+  // The kernel addresses a lattice row with 32-bit byte offsets.
+  if ((int64_t)L.L1 * P->n_sub * P->Rp * 2 * (int64_t)P->tsize >= (int64_t(1) << 31)) return KPM_E_UNSUPPORTED;
+  // Up to 8 chunks (128 bytes) of each site, fewer where the workgroup would span
+  // less than 4 KS thread columns; the largest workgroup whose rings fit the LDS.
+  int ew = (int)std::min<int64_t>(P->E, 8), block = kMaxStepBlock;
+  for (; block >= 64; block -= 64) {
+    ew = (int)std::min<int64_t>(P->E, 8);
+    while (ew > 1 && block / (P->n_sub * ew) < 4 * ks) ew >>= 1;
+    const int tx = block / (P->n_sub * ew);
+    const size_t rings = (4 * (size_t)ks * (tx + 2) + 1) * P->n_sub * ew * 16;
+    if (tx >= 4 * ks && rings <= (size_t)lds_max) {
+      H->Tx = tx;
+      H->lds_bytes = rings;
+      break;
+    }
+  }
+  if (block < 64) return KPM_E_UNSUPPORTED;
+  const int xstep = H->Tx - 2 * (ks - 1);
+  const int n_rg = (int)ceil_div(P->E, ew);
+  // Rows per tile: the fewest rounds of concurrent workgroups (one per CU, by LDS),
+  // each costing the tile's rows and the 3 KS - 3 of its skewed start and drain.
+  const int64_t conc = (int64_t)n_cu * std::max(1, std::min(kMaxStepBlock / block, (int)(lds_max / H->lds_bytes)));
+  int best_ty = 1;
+  int64_t best = INT64_MAX;
+  for (int ty = 1; ty <= std::min(256, L.L2); ++ty) {
+    const int64_t nt = (int64_t)n_rg * ceil_div(L.L2, ty) * ceil_div(L.L1, xstep);
+    const int64_t cost = ceil_div(nt, conc) * (ceil_div(ty + 3 * ks - 3, 4) * 4);
+    if (cost <= best) {
+      best = cost;
+      best_ty = ty;
+    }
+  }
+  std::vector<int4> tiles;
+  for (int g = 0; g < n_rg; ++g)
+    for (int y0 = 0; y0 < L.L2; y0 += best_ty)
+      for (int x0 = 0; x0 < L.L1; x0 += xstep) tiles.push_back(make_int4(0, g, x0, y0));
+  H->block = block;
+  H->Ew = ew;
+  H->Ty = best_ty;
+  H->n_tiles = (int)tiles.size();
+  H->grid = (int)(ceil_div(std::min<int64_t>((int64_t)tiles.size(), conc), 8) * 8);
+  H->fn = P->prec == KPM_FP32 ? pick_history_kind<float>(P->kind, P->has_onsite, P->has_mask, P->has_phase)
+                              : pick_history_kind<double>(P->kind, P->has_onsite, P->has_mask, P->has_phase);
+  hipError_t e = dev_malloc(&H->tiles, tiles.size() * sizeof(int4));
+  if (e == hipSuccess)
+    e = KPM_HIP(hipMemcpy(H->tiles, tiles.data(), tiles.size() * sizeof(int4), hipMemcpyHostToDevice));
+  if (e != hipSuccess) {
+    set_error("history sweep setup: %s", hipGetErrorString(e));
+    (void)hipGetLastError();
+    hist_plan_free(H);
+    return hip_status(e);
+  }
+  return KPM_OK;
+}
+
+void hist_plan_free(HistPlan* H) {
+  (void)dev_free(H->tiles);
+  *H = HistPlan();
+}
+
+template <typename T>
+static hipError_t history_launch(const kpm_plan* P, const HistPlan& H, hipStream_t s, const void* v, const void* w,
+                                 int nlev, void* const* out) {
+  SweepArgs<T> a = {};
+  a.lats = (const LatDev<T>*)P->latdev;
+  a.tiles = H.tiles;
+  a.n_tiles = H.n_tiles;
+  a.v = (const T*)v;
+  a.w = (const T*)(w ? w : v);
+  a.onsite = (const T*)P->onsite;
+  a.mask = P->mask;
+  a.phase = (const T*)P->phase;
+  a.a1 = w ? (T)2 : (T)1;
+  a.b1 = w ? (T)1 : (T)0;
+  a.read_w1 = w ? 1 : 0;
+  a.nlev = nlev;
+  a.Tx = H.Tx;
+  a.Ty = H.Ty;
+  a.E = P->E;
+  a.Ew = H.Ew;
+  a.Rp = P->Rp;
+  for (int l = 0; l < kHistSteps; ++l) a.hist[l] = (T*)out[l < nlev ? l : 0];
+  void* args[] = {&a};
+  return after_call(hipLaunchKernel(H.fn, dim3(H.grid), dim3(H.block), args, H.lds_bytes, s));
+}
+
+hipError_t history_sweep(const kpm_plan* P, const HistPlan& H, hipStream_t s, const void* v, const void* w, int nlev,
+                         void* const* out) {
+  if (nlev < 1 || nlev > kHistSteps || H.fn == nullptr) return hipErrorInvalidValue;
+  return P->prec == KPM_FP32 ? history_launch<float>(P, H, s, v, w, nlev, out)
+                             : history_launch<double>(P, H, s, v, w, nlev, out);
+}
+
+// T_n x0 for n = n0 .. n1 - 1 (n0 >= 1) into the buffers at(n), from T_{n0-1} and
+// T_{n0-2}: history sweeps where the plan has them, else single steps.  A sweep
+// forms at most max_levels levels (the caller's buffers allow that many beside the
+// two it reads).
+hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, int n1, int max_levels,
+                       const std::function<void*(int)>& at) {
+  hipError_t e = hipSuccess;
+  for (int n = n0; n < n1 && e == hipSuccess;) {
+    const void* v = at(n - 1);
+    const void* w = n >= 2 ? at(n - 2) : nullptr;
+    if (H && H->fn) {
+      const int nlev = std::min(std::min(kHistSteps, max_levels), n1 - n);
+      void* out[kHistSteps];
+      for (int l = 0; l < nlev; ++l) out[l] = at(n + l);
+      e = history_sweep(P, *H, s, v, w, nlev, out);
+      n += nlev;
+    } else {
+      StepLaunch S;
+      S.dots = 0;
+      S.v = v;
+      S.w = w;
+      S.out = at(n);
+      if (!w) {
+        S.read_w = 0; S.a = 1.0; S.b = 0.0;
+      }
+      e = plan_launch_step(P, s, S);
+      n += 1;
+    }
+  }
+  return e;
 }
 
 }  // namespace kpm
