@@ -102,12 +102,15 @@ typedef struct kpm_dos_params_t {
   int32_t num_sites;
 } kpm_dos_params_t;
 
-/* Optional launch shape of the Chebyshev step kernel (0 = library choice / autotune cache). */
+/* Optional launch shape of the Chebyshev step kernel (0 = library choice / autotune cache).  With block,
+ * rows, grid, kernel and chunks all 0, lattices too small to fill the chip with rows run on square patches
+ * held in LDS, 2..8 steps per launch; kpm_plan_info then gives the patch's cells as rows and tile_cells_x. */
 typedef struct kpm_tune_t {
   int32_t block;           /* threads per workgroup (64..512, multiple of 64); 0 = 512 for the sweep kernels
                               (less where their row rings would not fit in LDS), 256 otherwise */
-  int32_t rows;            /* lattice rows (along a2) per tile; 0 = the largest power of two <= 128 (sweep
-                              kernels) or <= 64 (single-step) that leaves >= 2048 tiles */
+  int32_t rows;            /* lattice rows (along a2) per tile; 0 = the fewest rounds of rows over the CUs, at
+                              most 256 (sweep kernels), or the largest power of two <= 64 that leaves >= 2048
+                              tiles (single-step) */
   int32_t grid;            /* persistent workgroups (multiple of 8); 0 = one per tile */
   int32_t use_graph;       /* 1 = replay the step loop as a captured hipGraph (default), 0 = eager */
   int32_t kernel;          /* 0 = default (5 where eligible, else 2), 1 = direct neighbour loads, 2 = LDS row
@@ -120,15 +123,17 @@ typedef struct kpm_tune_t {
 } kpm_tune_t;
 
 typedef struct kpm_plan_info_t {
-  int32_t n_steps;               /* recursion steps per run (ceil(M/2)); variants 3..6 launch once per 2..5 */
+  int32_t n_steps;               /* recursion steps per run (ceil(M/2)); variants 3..6 launch once per 2..5,
+                                    patches once per 2..8 */
   int32_t n_tiles;               /* tiles in the work list */
   int32_t grid, block, rows, tile_cells_x;
   int32_t r_padded;              /* vectors per orbital as stored (R rounded up) */
   int32_t kernel;                /* step kernel variant in use (1 direct, 2 LDS ring, 3..6 = 2..5 steps per
-                                    sweep) */
+                                    sweep; on patches the one that rows would take) */
   int64_t n_orbitals;            /* orbitals in the batch, vacancies included */
-  double bytes_per_step;         /* algorithmic HBM bytes per recursion step (variants 3..6: two vectors
-                                    and the site arrays in, two vectors out, per sweep of 2..5 steps) */
+  double bytes_per_step;         /* algorithmic HBM bytes per recursion step (variants 3..6 and
+                                    patches: two vectors and the site arrays in, two vectors out, per
+                                    launch) */
   double last_loop_ms;           /* step loop of the last run (hipEvents on the run's stream) */
   double last_run_ms;            /* whole last run (hipEvents) */
   int64_t n_active_total;        /* active orbitals summed over lattices (after the last run) */

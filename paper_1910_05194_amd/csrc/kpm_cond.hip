@@ -437,7 +437,7 @@ static int gamma1_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, doub
     if (e == hipSuccess && B > 0) e = ::kpm::dev_malloc(&hist, vec_b * (size_t)B);
   }
   if (e == hipSuccess && B > 0) {
-    st = hist_plan_create(P, &H);
+    st = hist_plan_create(P, B - 2, &H);
     if (st == KPM_E_UNSUPPORTED) st = KPM_OK;   // single steps
   }
   if (e == hipSuccess && st == KPM_OK) st = plan_set_vector_base(P, 0);
@@ -637,7 +637,7 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
   }
   HistPlan H4;
   if (e == hipSuccess) {
-    st = hist_plan_create(P, &H4);
+    st = hist_plan_create(P, B - 2, &H4);
     if (st == KPM_E_UNSUPPORTED) st = KPM_OK;   // single steps
   }
   void *V0 = nullptr, *Sc = nullptr, *acc = nullptr, *hist = nullptr;

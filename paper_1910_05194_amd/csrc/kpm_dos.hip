@@ -1140,12 +1140,15 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
     return KPM_E_INVALID;
   }
   P->variant = want;
-  if (P->variant >= 3) {
+  bool room = false;
+  {
     const double vec_b = (double)P->n_orb * P->Rp * 2 * P->tsize;
     size_t free_b = 0, total_b = 0;
     // Four vectors with 2 GB to spare, or (arena) with a quarter of the arena left for the rest.
-    const bool room = P->use_arena ? 4.0 * vec_b <= 0.75 * (double)P->arena_cap
-                                    : mem_available(&free_b, &total_b) == hipSuccess && (double)free_b > 4.0 * vec_b + 2.0e9;
+    room = P->use_arena ? 4.0 * vec_b <= 0.75 * (double)P->arena_cap
+                         : mem_available(&free_b, &total_b) == hipSuccess && (double)free_b > 4.0 * vec_b + 2.0e9;
+  }
+  if (P->variant >= 3) {
     // The sweep kernels address a lattice row with 32-bit offsets.
     bool rows_fit = true;
     for (int l = 0; l < n_lat; ++l)
@@ -1189,27 +1192,55 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
   }
   P->n_rg = (int)ceil_div(P->E, P->Ew);
   // Cells a tile owns along n1 (a sweep kernel spends KS - 1 thread columns per side on halos).
-  const int xstep = P->Tx - 2 * (P->sweep - 1);
+  int xstep = P->Tx - 2 * (P->sweep - 1);
+  int dev = 0, n_cu = 256, cus = 0;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
+    n_cu = cus;
+  double us_per_step = 0.0;   // modelled
   if (!(tune && tune->rows > 0)) {
-    // Default rows per tile: the largest power of two <= 64 (128 for the sweep
-    // kernels, whose bands re-read 2 KS halo rows) that still gives at least
-    // 2048 tiles (8 per CU), so that small lattices fill the chip.
-    int ty = P->variant >= 3 ? 128 : 64;
-    while (ty > 1) {
-      int64_t nt = 0;
-      for (int l = 0; l < n_lat; ++l) nt += ceil_div(lat[l].L1, xstep) * P->n_rg * ceil_div(lat[l].L2, ty);
-      if (nt >= 2048) break;
-      ty >>= 1;
+    if (P->variant >= 3) {
+      const int64_t conc = (int64_t)n_cu * std::max(1, kMaxStepBlock / P->block);
+      us_per_step = sweep_rows(P->lats, P->sweep, xstep, P->n_rg, conc, &P->Ty);
+    } else {
+      // Default rows per tile of the single-step kernels: the largest power of two
+      // <= 64 that still gives at least 2048 tiles (8 per CU), so that small
+      // lattices fill the chip.
+      int ty = 64;
+      while (ty > 1) {
+        int64_t nt = 0;
+        for (int l = 0; l < n_lat; ++l) nt += ceil_div(lat[l].L1, xstep) * P->n_rg * ceil_div(lat[l].L2, ty);
+        if (nt >= 2048) break;
+        ty >>= 1;
+      }
+      P->Ty = ty;
+      // A launch, and three vectors at the rate these kernels reach (spinful 512 x 512,
+      // 8 vectors: 46 us; 64 x 64, 4 vectors: 5.7 us).
+      us_per_step = 4.6 + 3.0 * (double)P->n_orb * P->Rp * 2 * P->tsize / 4.8e6;
     }
-    P->Ty = ty;
+  }
+  // Patches where the library chooses the whole shape and the model sees a clear gain.
+  const bool shape_given = tune && (tune->block > 0 || tune->rows > 0 || tune->grid > 0 || tune->kernel > 0 || tune->chunks > 0);
+  if (!shape_given && room && patch_shape(P, false, patch_steps(P->kind), lds_max, n_cu, &P->patch_sh) &&
+      P->patch_sh.us_per_step < kPatchGain * us_per_step) {
+    P->patch = true;
+    P->sweep = P->patch_sh.ks;
+    P->block = kPatchBlock;
+    P->Ew = 1 << P->patch_sh.lgw;
+    P->n_rg = (int)ceil_div(P->E, P->Ew);
+    P->Tx = xstep = P->patch_sh.px;
+    P->Ty = P->patch_sh.py;
   }
 
-  // Tile work list ordered (lattice, r-group, row band, column band).
+  // Tile work list ordered (lattice, r-group, row band, column band); patches with
+  // the r-groups innermost: the chunks of one site share cache lines, and the
+  // workgroups of neighbouring tiles an L2.
   std::vector<int4> tiles;
   for (int l = 0; l < n_lat; ++l)
-    for (int g = 0; g < P->n_rg; ++g)
+    for (int go = 0; go < (P->patch ? 1 : P->n_rg); ++go)
       for (int y0 = 0; y0 < lat[l].L2; y0 += P->Ty)
-        for (int x0 = 0; x0 < lat[l].L1; x0 += xstep) tiles.push_back(make_int4(l, g, x0, y0));
+        for (int x0 = 0; x0 < lat[l].L1; x0 += xstep)
+          for (int g = go; g < (P->patch ? P->n_rg : go + 1); ++g) tiles.push_back(make_int4(l, g, x0, y0));
   P->n_tiles = (int)tiles.size();
   // Default: a persistent grid of at most 2048 workgroups (8 per CU).
   int grid = (tune && tune->grid > 0) ? tune->grid : (int)std::min<int64_t>(2048, ceil_div(P->n_tiles, 8) * 8);
@@ -1265,7 +1296,9 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
   P->steps_per_chunk = (int)std::max<double>(1.0, std::min<double>(P->n_steps, std::floor(budget / part_step_bytes)));
   // A sweep kernel writes the partials of its KS steps into one chunk.
   if (P->sweep > 1)
-    P->steps_per_chunk = std::max(P->sweep, P->steps_per_chunk - P->steps_per_chunk % P->sweep);
+    P->steps_per_chunk = P->steps_per_chunk == P->n_steps
+                             ? (int)ceil_div(P->n_steps, P->sweep) * P->sweep
+                             : std::max(P->sweep, P->steps_per_chunk - P->steps_per_chunk % P->sweep);
 
   // Algorithmic bytes per step: read v_n and v_{n-1}, write v_{n+1}, per-site
   // arrays; a sweep kernel reads two vectors and the site arrays and writes
@@ -1397,7 +1430,9 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
   const size_t ring_bytes = (size_t)P->block * 2 * P->NC * sizeof(double) +
                             4 * (size_t)(P->Tx + 2) * P->n_sub * P->n_spin * P->Ew * 16;
   if (P->variant == 2 && ring_bytes > 65536) P->variant = 1;
-  if (P->sweep > 1) {
+  if (P->patch) {
+    P->lds_bytes = P->patch_sh.lds_bytes;
+  } else if (P->sweep > 1) {
     // v_n ring and one ring per inner level; the moment flush reuses the same LDS between tiles.
     const size_t rings = (4 * (size_t)P->sweep * (P->Tx + 2) + 1) * P->n_sub * P->Ew * 16;
     P->lds_bytes = std::max(rings, (size_t)P->block * 2 * P->NC * sizeof(double));
@@ -1567,7 +1602,10 @@ static hipError_t launch_loop_sweep(kpm_plan* P, hipStream_t s) {
   for (int k = 0; k < P->n_steps; k += P->sweep) {
     const int nlev = std::min(P->sweep, P->n_steps - k);
     double* p0 = P->part + (int64_t)(k - chunk0) * part_stride;
-    hipError_t le = (P->prec == KPM_FP32)
+    void* outs[2] = {fa, fb};
+    hipError_t le = P->patch ? patch_run(P, P->patch_sh, s, P->tiles, P->slot_of, P->n_tiles, cur,
+                                         k == 0 ? nullptr : prev, nlev, outs, p0, part_stride)
+                    : (P->prec == KPM_FP32)
                         ? launch_sweep_t<float>(P, s, cur, prev, fa, fb, k == 0 ? 1 : 0, nlev, p0, part_stride)
                         : launch_sweep_t<double>(P, s, cur, prev, fa, fb, k == 0 ? 1 : 0, nlev, p0, part_stride);
     if (le != hipSuccess) return le;

@@ -367,14 +367,13 @@ static hipError_t evolve_loop(kpm_plan* P, const kpm_evolve_params_t* p, const C
   if (e == hipSuccess) e = hipEventCreate(&ev1);
   if (e == hipSuccess) e = hipEventRecord(ev0, s);
   if (e == hipSuccess) e = observe(0);
-  // Algorithmic bytes: a single step reads v_n (neighbours from cache) and
-  // v_(n-1), writes v_(n+1), reads the per-site arrays, a history sweep of up to
-  // kHistSteps steps the same with one vector written per step; a flush reads its
-  // history vectors and writes psi(t + dt) (reading it too after the first).
+  // Algorithmic bytes, counted in single steps also where a launch makes several: a
+  // recursion step reads v_n (neighbours from cache) and v_(n-1), writes v_(n+1),
+  // reads the per-site arrays; a flush reads its history vectors and writes
+  // psi(t + dt) (reading it too after the first).
   const double site_b = (double)n_sites * ((P->has_onsite ? (double)sizeof(T) : 0.0) + (P->has_mask ? 1.0 : 0.0));
   const int n_flush = (M + B - 1) / B;
-  const double launches = H4.fn ? (double)ceil_div(M - 1, kHistSteps) : (double)(M - 1);
-  const double step_b = launches * (2.0 * (double)vec_b + site_b) + (double)(M - 1) * (double)vec_b + ((double)M + 2.0 * n_flush - 1.0) * (double)vec_b;
+  const double step_b = (double)(M - 1) * (3.0 * (double)vec_b + site_b) + ((double)M + 2.0 * n_flush - 1.0) * (double)vec_b;
   for (int k = 1; k < p->num_points && e == hipSuccess; ++k) {
     const std::function<void*(int)> at = hvec;
     for (int n0 = 0; n0 < M && e == hipSuccess; n0 += B) {
@@ -446,7 +445,7 @@ static int evolve_run(const kpm_lattice_t* lat, const kpm_evolve_params_t* p, do
   HistPlan H4;
   int st = KPM_OK;
   if (e == hipSuccess) {
-    st = hist_plan_create(P, &H4);
+    st = hist_plan_create(P, B - 2, &H4);
     if (st == KPM_E_UNSUPPORTED) st = KPM_OK;   // single steps
     if (st != KPM_OK) {
       plan_free(P);

@@ -55,17 +55,42 @@ void chain_plan_free(ChainPlan* C);
 hipError_t chain_run(const kpm_plan* P, const ChainPlan& C, hipStream_t s, int mode, void* v0, void* w0,
                      int n_levels, void* blk, void* blk_lo, int64_t blk_rows, int vdir, double vel_scale,
                      double* bytes);
-// History sweeps (kpm_sweep.hip, spinless lattices): up to kHistSteps recursion
-// steps per launch, every T_n x written to a buffer of its own.
-// The step kernels' single steps serve where it has no shape (fn == nullptr).
+// Patch kernels (kpm_patch.hip): up to patch_steps(kind) recursion steps per launch
+// on lattices too small to fill the chip with rows.
+constexpr int kPatchBlock = 512;
+constexpr int kPatchSteps = 8;
+constexpr double kPatchGain = 0.85;   // of the rows' modelled time, to allow for the model's error
+constexpr int kPatchRounds = 4;   // at most this many patches per CU
+constexpr int patch_steps(int kind) { return kind == KPM_HONEYCOMB_SPIN ? 4 : kPatchSteps; }
+struct PatchShape {
+  int px = 0, py = 0, ks = 0, ex = 0, spt = 0, lgw = 0;
+  size_t lds_bytes = 0;
+  void* fn = nullptr;
+  double us_per_step = 0.0;   // modelled
+};
+// The best patch shape of at most max_steps steps for the plan's lattices; false where none fits.
+bool patch_shape(const kpm_plan* P, bool hist, int max_steps, int lds_max, int n_cu, PatchShape* best);
+// Steps n .. n + nlev - 1 from v = v_n and w = v_{n-1} (nullptr: n = 0).  With part
+// (products of each step): out[0] = v_{n+nlev-1}, out[1] = v_{n+nlev}; without:
+// out[l] = v_{n+l+1}.
+hipError_t patch_run(const kpm_plan* P, const PatchShape& S, hipStream_t s, const int4* tiles, const int* slot_of,
+                     int n_tiles, const void* v, const void* w, int nlev, void* const* out, double* part,
+                     int64_t part_stride);
+// History sweeps: several recursion steps per launch, every T_n x written to a
+// buffer of its own, on patches or (spinless lattices, kpm_sweep.hip) in row sweeps
+// of up to kHistSteps.  Single steps serve where neither has a shape (fn == nullptr).
 struct HistPlan {
+  PatchShape patch;   // patch.fn: patches instead of row sweeps
+  int levels = 0;     // steps per launch
   int block = 0, Tx = 0, Ty = 0, Ew = 0, grid = 0, n_tiles = 0;
   size_t lds_bytes = 0;
   int4* tiles = nullptr;
   void* fn = nullptr;
 };
-// KPM_E_UNSUPPORTED (spinful lattice, no tile shape fits): the caller runs single steps.
-int hist_plan_create(const kpm_plan* P, HistPlan* H);
+// Rows per tile of a sweep (at most 256) and its modelled time per step (us).
+double sweep_rows(const std::vector<kpm_lattice_t>& lats, int ks, int xstep, int n_rg, int64_t conc, int* ty);
+// For launches of at most max_levels steps.  KPM_E_UNSUPPORTED: the caller runs single steps.
+int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H);
 void hist_plan_free(HistPlan* H);
 hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, int n1, int max_levels,
                        const std::function<void*(int)>& at);
@@ -122,6 +147,8 @@ struct kpm_plan {
   int variant = 2;             // 1 = direct-load step kernel, 2 = LDS row ring, 3..6 = 2..5 steps per sweep
   int sweep = 1;               // Chebyshev steps per launch (variant - 1 for the sweep kernels, else 1)
   size_t lds_bytes = 0;
+  bool patch = false;          // the steps run on patches (sweep of them per launch)
+  kpm::PatchShape patch_sh;
   int64_t r_base = 0;          // global index of the plan's first random vector
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t graph_loop = nullptr;

@@ -52,6 +52,67 @@ __device__ inline void cmul_acc(T& ore, T& oim, T are, T aim, T bre, T bim) {
   oim = fma(aim, bre, oim);
 }
 
+// out = a (H~ v)_i - b w_i at one site (one spin), and, when acc (a uniform
+// condition: the row belongs to the tile), the doubling dot products <v|v>,
+// <out|v> added to the FP64 sums pv, pw.  The products are formed in FP64
+// from the vectors' values (exact for FP32 vectors).  Threads outside the
+// tile's interior add values that may be anything (NaN included); their sums
+// are discarded once per tile.  With PHASE the neighbour k enters with the
+// complex coefficient (hre[k], him[k]) = hop exp(i theta_k) of the site's
+// column, else with hop.
+// HIST: no products, and the single-step kernels' arithmetic to the bit: there the
+// first neighbour's product is rounded and the on-site one fused (without HIST the
+// other way round: two products meet, so the FMAs are written out and not left to the
+// compiler), and with PHASE each neighbour's term is rounded before it is added.
+template <typename T, int KIND, bool PHASE, bool HIST>
+__device__ inline void sweep_site(T a, T b, bool read_w, T hop, const T* hre, const T* him, T ons, bool alive,
+                                  const Pack<T>& vo, const Pack<T>& wo, const Pack<T> (&vn)[KindTraits<KIND>::NNB],
+                                  Pack<T>& out, bool acc, double* pv, double* pw) {
+  constexpr int NC = Pack<T>::NC;
+  constexpr int NNB = KindTraits<KIND>::NNB;
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    T hr = ons * vo.v[2 * j], hi = ons * vo.v[2 * j + 1];
+#pragma unroll
+    for (int k = 0; k < NNB; ++k) {
+      if constexpr (PHASE && HIST) {
+        T tr = 0, ti = 0;
+        cmul_acc(tr, ti, hre[k], him[k], vn[k].v[2 * j], vn[k].v[2 * j + 1]);
+        hr += tr;
+        hi += ti;
+      } else if constexpr (PHASE) {
+        cmul_acc(hr, hi, hre[k], him[k], vn[k].v[2 * j], vn[k].v[2 * j + 1]);
+      } else if (HIST && k == 0) {
+        hr = fma(ons, vo.v[2 * j], hop * vn[k].v[2 * j]);
+        hi = fma(ons, vo.v[2 * j + 1], hop * vn[k].v[2 * j + 1]);
+      } else {
+        hr = fma(hop, vn[k].v[2 * j], hr);
+        hi = fma(hop, vn[k].v[2 * j + 1], hi);
+      }
+    }
+    T orr = a * hr, oi = a * hi;
+    if (read_w) {
+      orr -= b * wo.v[2 * j];
+      oi -= b * wo.v[2 * j + 1];
+    }
+    if (!alive) {
+      orr = 0;
+      oi = 0;
+    }
+    out.v[2 * j] = orr;
+    out.v[2 * j + 1] = oi;
+  }
+  // One uniform branch for all of the site's products.
+  if (!HIST && acc) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const double xr = vo.v[2 * j], xi = vo.v[2 * j + 1];
+      pv[j] = fma(xr, xr, fma(xi, xi, pv[j]));
+      pw[j] = fma((double)out.v[2 * j], xr, fma((double)out.v[2 * j + 1], xi, pw[j]));
+    }
+  }
+}
+
 // Reduce the per-thread dot products of one moment slot over the workgroup
 // (fixed-order LDS tree) and write them to part[slot].
 template <int NC>

@@ -35,62 +35,6 @@ namespace kpm {
 // first nlev levels only (the last, short sweep of a recursion).
 // ---------------------------------------------------------------------------
 
-// out = a (H~ v)_i - b w_i at one site (one spin), and, when acc (a uniform
-// condition: the row belongs to the tile), the doubling dot products <v|v>,
-// <out|v> added to the FP64 sums pv, pw.  The products are formed in FP64
-// from the vectors' values (exact for FP32 vectors).  Threads outside the
-// tile's interior add values that may be anything (NaN included); their sums
-// are discarded once per tile.  With PHASE the neighbour k enters with the
-// complex coefficient (hre[k], him[k]) = hop exp(i theta_k) of the site's
-// column, else with hop.
-// HIST: no products, and with PHASE each neighbour's term is rounded before it
-// is added (the single-step kernels' arithmetic, to the bit).
-template <typename T, int KIND, bool PHASE, bool HIST>
-__device__ inline void sweep_site(T a, T b, bool read_w, T hop, const T* hre, const T* him, T ons, bool alive,
-                                  const Pack<T>& vo, const Pack<T>& wo, const Pack<T> (&vn)[KindTraits<KIND>::NNB],
-                                  Pack<T>& out, bool acc, double* pv, double* pw) {
-  constexpr int NC = Pack<T>::NC;
-  constexpr int NNB = KindTraits<KIND>::NNB;
-#pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    T hr = ons * vo.v[2 * j], hi = ons * vo.v[2 * j + 1];
-#pragma unroll
-    for (int k = 0; k < NNB; ++k) {
-      if constexpr (PHASE && HIST) {
-        T tr = 0, ti = 0;
-        cmul_acc(tr, ti, hre[k], him[k], vn[k].v[2 * j], vn[k].v[2 * j + 1]);
-        hr += tr;
-        hi += ti;
-      } else if constexpr (PHASE) {
-        cmul_acc(hr, hi, hre[k], him[k], vn[k].v[2 * j], vn[k].v[2 * j + 1]);
-      } else {
-        hr += hop * vn[k].v[2 * j];
-        hi += hop * vn[k].v[2 * j + 1];
-      }
-    }
-    T orr = a * hr, oi = a * hi;
-    if (read_w) {
-      orr -= b * wo.v[2 * j];
-      oi -= b * wo.v[2 * j + 1];
-    }
-    if (!alive) {
-      orr = 0;
-      oi = 0;
-    }
-    out.v[2 * j] = orr;
-    out.v[2 * j + 1] = oi;
-  }
-  // One uniform branch for all of the site's products.
-  if (!HIST && acc) {
-#pragma unroll
-    for (int j = 0; j < NC; ++j) {
-      const double xr = vo.v[2 * j], xi = vo.v[2 * j + 1];
-      pv[j] = fma(xr, xr, fma(xi, xi, pv[j]));
-      pw[j] = fma((double)out.v[2 * j], xr, fma((double)out.v[2 * j + 1], xi, pw[j]));
-    }
-  }
-}
-
 // SHAPE 0: the tile shape (chunks per site Ew, thread columns Tx) comes from
 // the arguments.  SHAPE 1: 512 threads, 8 chunks per site (the shape the
 // benchmarked workloads run): compile-time constants, so every LDS ring
@@ -574,21 +518,44 @@ void* sweep_kernel_fn(int prec, int kind, int ks, bool onsite, bool mask, bool p
 
 namespace kpm {
 
-int hist_plan_create(const kpm_plan* P, HistPlan* H) {
+// Rows per tile: the fewest rounds of concurrent workgroups (conc of them; the rings
+// leave room for one per CU), each costing the tile's rows and the 3 KS - 3 of its
+// skewed start and drain, in groups of four (the unrolled loop).  The time is a
+// launch and 1.25 us a row: measured 16.3 us per launch of 12 rows (64 x 64, 4 vectors,
+// FP64), 30.8 of 20 (512 x 512, 4, FP32).  The former rule of at least 2048 tiles gave a
+// 256 x 256 lattice one-row tiles, three rounds of them: 13.4 us a step, now 6.3.
+double sweep_rows(const std::vector<kpm_lattice_t>& lats, int ks, int xstep, int n_rg, int64_t conc, int* ty) {
+  int64_t best = INT64_MAX;
+  *ty = 1;
+  for (int t = 1; t <= 256; ++t) {
+    int64_t nt = 0;
+    for (const kpm_lattice_t& L : lats) nt += n_rg * ceil_div(L.L2, t) * ceil_div(L.L1, xstep);
+    const int64_t cost = ceil_div(nt, conc) * (ceil_div(t + 3 * ks - 3, 4) * 4);
+    if (cost <= best) {
+      best = cost;
+      *ty = t;
+    }
+  }
+  return (4.0 + 1.25 * (double)best) / ks;
+}
+
+int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
   *H = HistPlan();
-  if (P->n_spin != 1 || P->n_lat != 1) return KPM_E_UNSUPPORTED;
+  if (P->n_lat != 1) return KPM_E_UNSUPPORTED;
   int dev = 0, lds_max = 65536, n_cu = 256, v = 0;
   if (hipGetDevice(&dev) == hipSuccess) {
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0) lds_max = v;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) n_cu = v;
   }
   const kpm_lattice_t& L = P->lats[0];
-  constexpr int ks = kHistSteps;
-  // The kernel addresses a lattice row with 32-bit byte offsets.
-  if ((int64_t)L.L1 * P->n_sub * P->Rp * 2 * (int64_t)P->tsize >= (int64_t(1) << 31)) return KPM_E_UNSUPPORTED;
+  const int ks = kHistSteps;
+  const double vec_b = (double)P->n_orb * P->Rp * 2 * P->tsize;
+  double us = 4.6 + 3.0 * vec_b / 4.8e6;   // single steps, as for the density of states
+  // Row sweeps without a spin; the kernel addresses a lattice row with 32-bit byte offsets.
+  const bool rows = P->n_spin == 1 && (int64_t)L.L1 * P->n_sub * P->Rp * 2 * (int64_t)P->tsize < (int64_t(1) << 31);
   // Up to 8 chunks (128 bytes) of each site, fewer where the workgroup would span
   // less than 4 KS thread columns; the largest workgroup whose rings fit the LDS.
-  int ew = (int)std::min<int64_t>(P->E, 8), block = kMaxStepBlock;
+  int ew = (int)std::min<int64_t>(P->E, 8), block = rows ? kMaxStepBlock : 0, ty = 1;
   for (; block >= 64; block -= 64) {
     ew = (int)std::min<int64_t>(P->E, 8);
     while (ew > 1 && block / (P->n_sub * ew) < 4 * ks) ew >>= 1;
@@ -600,33 +567,43 @@ int hist_plan_create(const kpm_plan* P, HistPlan* H) {
       break;
     }
   }
-  if (block < 64) return KPM_E_UNSUPPORTED;
-  const int xstep = H->Tx - 2 * (ks - 1);
-  const int n_rg = (int)ceil_div(P->E, ew);
-  // Rows per tile: the fewest rounds of concurrent workgroups (one per CU, by LDS),
-  // each costing the tile's rows and the 3 KS - 3 of its skewed start and drain.
-  const int64_t conc = (int64_t)n_cu * std::max(1, std::min(kMaxStepBlock / block, (int)(lds_max / H->lds_bytes)));
-  int best_ty = 1;
-  int64_t best = INT64_MAX;
-  for (int ty = 1; ty <= std::min(256, L.L2); ++ty) {
-    const int64_t nt = (int64_t)n_rg * ceil_div(L.L2, ty) * ceil_div(L.L1, xstep);
-    const int64_t cost = ceil_div(nt, conc) * (ceil_div(ty + 3 * ks - 3, 4) * 4);
-    if (cost <= best) {
-      best = cost;
-      best_ty = ty;
-    }
+  int xstep = 1, n_rg = 1;
+  int64_t conc = n_cu;
+  if (block >= 64) {
+    xstep = H->Tx - 2 * (ks - 1);
+    n_rg = (int)ceil_div(P->E, ew);
+    conc = (int64_t)n_cu * std::max(1, std::min(kMaxStepBlock / block, (int)(lds_max / H->lds_bytes)));
+    us = sweep_rows(P->lats, ks, xstep, n_rg, conc, &ty);
+  }
+  // A launch writes as many vectors as it makes steps: at 5 TB/s on top.
+  if (patch_shape(P, true, max_levels, lds_max, n_cu, &H->patch) &&
+      H->patch.us_per_step + (block >= 64 ? 0.5 * vec_b / 5.0e6 : 0.0) < kPatchGain * us) {
+    block = kPatchBlock;
+    ew = 1 << H->patch.lgw;
+    n_rg = (int)ceil_div(P->E, ew);
+    xstep = H->patch.px;
+    ty = H->patch.py;
+    H->levels = H->patch.ks;
+  } else {
+    H->patch = PatchShape();
+    if (block < 64) return KPM_E_UNSUPPORTED;
+    H->levels = kHistSteps;
   }
   std::vector<int4> tiles;
-  for (int g = 0; g < n_rg; ++g)
-    for (int y0 = 0; y0 < L.L2; y0 += best_ty)
-      for (int x0 = 0; x0 < L.L1; x0 += xstep) tiles.push_back(make_int4(0, g, x0, y0));
+  // Patches with the r-groups innermost (the chunks of one site share cache lines).
+  const bool inner_g = H->patch.fn != nullptr;
+  for (int go = 0; go < (inner_g ? 1 : n_rg); ++go)
+    for (int y0 = 0; y0 < L.L2; y0 += ty)
+      for (int x0 = 0; x0 < L.L1; x0 += xstep)
+        for (int g = go; g < (inner_g ? n_rg : go + 1); ++g) tiles.push_back(make_int4(0, g, x0, y0));
   H->block = block;
   H->Ew = ew;
-  H->Ty = best_ty;
+  H->Ty = ty;
   H->n_tiles = (int)tiles.size();
   H->grid = (int)(ceil_div(std::min<int64_t>((int64_t)tiles.size(), conc), 8) * 8);
-  H->fn = P->prec == KPM_FP32 ? pick_history_kind<float>(P->kind, P->has_onsite, P->has_mask, P->has_phase)
-                              : pick_history_kind<double>(P->kind, P->has_onsite, P->has_mask, P->has_phase);
+  H->fn = H->patch.fn          ? H->patch.fn
+          : P->prec == KPM_FP32 ? pick_history_kind<float>(P->kind, P->has_onsite, P->has_mask, P->has_phase)
+                                : pick_history_kind<double>(P->kind, P->has_onsite, P->has_mask, P->has_phase);
   hipError_t e = dev_malloc(&H->tiles, tiles.size() * sizeof(int4));
   if (e == hipSuccess)
     e = KPM_HIP(hipMemcpy(H->tiles, tiles.data(), tiles.size() * sizeof(int4), hipMemcpyHostToDevice));
@@ -672,7 +649,8 @@ static hipError_t history_launch(const kpm_plan* P, const HistPlan& H, hipStream
 
 hipError_t history_sweep(const kpm_plan* P, const HistPlan& H, hipStream_t s, const void* v, const void* w, int nlev,
                          void* const* out) {
-  if (nlev < 1 || nlev > kHistSteps || H.fn == nullptr) return hipErrorInvalidValue;
+  if (nlev < 1 || nlev > H.levels || H.fn == nullptr) return hipErrorInvalidValue;
+  if (H.patch.fn) return patch_run(P, H.patch, s, H.tiles, nullptr, H.n_tiles, v, w, nlev, out, nullptr, 0);
   return P->prec == KPM_FP32 ? history_launch<float>(P, H, s, v, w, nlev, out)
                              : history_launch<double>(P, H, s, v, w, nlev, out);
 }
@@ -688,8 +666,8 @@ hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, in
     const void* v = at(n - 1);
     const void* w = n >= 2 ? at(n - 2) : nullptr;
     if (H && H->fn) {
-      const int nlev = std::min(std::min(kHistSteps, max_levels), n1 - n);
-      void* out[kHistSteps];
+      const int nlev = std::min(std::min(H->levels, max_levels), n1 - n);
+      void* out[kPatchSteps];
       for (int l = 0; l < nlev; ++l) out[l] = at(n + l);
       e = history_sweep(P, *H, s, v, w, nlev, out);
       n += nlev;
