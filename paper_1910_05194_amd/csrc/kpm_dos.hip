@@ -1197,26 +1197,46 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
   if (hipGetDevice(&dev) == hipSuccess &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
     n_cu = cus;
+  // LDS: the ring variant needs 4 rows of (Tx + 2) cells (fall back to direct
+  // loads when that exceeds 64 KiB); a sweep kernel its row rings (below).
+  const size_t flush_bytes = (size_t)P->block * 2 * P->NC * sizeof(double);
+  const size_t ring_bytes = flush_bytes + 4 * (size_t)(P->Tx + 2) * P->n_sub * P->n_spin * P->Ew * 16;
+  if (P->variant == 2 && ring_bytes > 65536) P->variant = 1;
+  P->step_fn = (P->prec == KPM_FP32)
+                   ? pick_step_kind<float, false>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase)
+                   : pick_step_kind<double, false>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase);
+  P->step_fn_vel = (P->prec == KPM_FP32)
+                       ? pick_step_kind<float, true>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase)
+                       : pick_step_kind<double, true>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase);
+  if (P->variant < 3) P->lds_bytes = (P->variant == 2) ? ring_bytes : flush_bytes;
   double us_per_step = 0.0;   // modelled
   if (!(tune && tune->rows > 0)) {
     if (P->variant >= 3) {
       const int64_t conc = (int64_t)n_cu * std::max(1, kMaxStepBlock / P->block);
       us_per_step = sweep_rows(P->lats, P->sweep, xstep, P->n_rg, conc, &P->Ty);
     } else {
-      // Default rows per tile of the single-step kernels: the largest power of two
-      // <= 64 that still gives at least 2048 tiles (8 per CU), so that small
-      // lattices fill the chip.
-      int ty = 64;
-      while (ty > 1) {
-        int64_t nt = 0;
-        for (int l = 0; l < n_lat; ++l) nt += ceil_div(lat[l].L1, xstep) * P->n_rg * ceil_div(lat[l].L2, ty);
-        if (nt >= 2048) break;
-        ty >>= 1;
+      // Rows per tile of the single-step kernels: the fewest rounds of the workgroups
+      // that fit the chip, each costing its rows and three of start (two halo rows, the
+      // first loads).  The largest power of two that left 2048 tiles instead gave a
+      // spinful 512 x 512 lattice with 8 vectors four rounds of 4 rows: 46 us a step,
+      // with one of 16 35 us (3 vectors of 67 MB: 5.7 TB/s).
+      int occ = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, P->step_fn, P->block, P->lds_bytes) != hipSuccess || occ < 1) {
+        (void)hipGetLastError();
+        occ = std::max(1, kMaxStepBlock / P->block);
       }
-      P->Ty = ty;
-      // A launch, and three vectors at the rate these kernels reach (spinful 512 x 512,
-      // 8 vectors: 46 us; 64 x 64, 4 vectors: 5.7 us).
-      us_per_step = 4.6 + 3.0 * (double)P->n_orb * P->Rp * 2 * P->tsize / 4.8e6;
+      int64_t best = INT64_MAX;
+      for (int t = 1; t <= 64; ++t) {
+        int64_t nt = 0;
+        for (int l = 0; l < n_lat; ++l) nt += ceil_div(lat[l].L1, xstep) * P->n_rg * ceil_div(lat[l].L2, t);
+        const int64_t cost = ceil_div(nt, (int64_t)n_cu * occ) * (t + 3);
+        if (cost <= best) {
+          best = cost;
+          P->Ty = t;
+        }
+      }
+      // A launch, and the rows' latency or three vectors at the rate these kernels reach.
+      us_per_step = 4.2 + std::max(0.5 * (double)best, 3.0 * (double)P->n_orb * P->Rp * 2 * P->tsize / 6.0e6);
     }
   }
   // Patches where the library chooses the whole shape and the model sees a clear gain.
@@ -1425,28 +1445,15 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
     delete P;
     return ::kpm::hip_status(e);
   }
-  // LDS: the ring variant needs 4 rows of (Tx + 2) cells (fall back to direct
-  // loads when that exceeds 64 KiB); a sweep kernel its row rings.
-  const size_t ring_bytes = (size_t)P->block * 2 * P->NC * sizeof(double) +
-                            4 * (size_t)(P->Tx + 2) * P->n_sub * P->n_spin * P->Ew * 16;
-  if (P->variant == 2 && ring_bytes > 65536) P->variant = 1;
   if (P->patch) {
     P->lds_bytes = P->patch_sh.lds_bytes;
   } else if (P->sweep > 1) {
     // v_n ring and one ring per inner level; the moment flush reuses the same LDS between tiles.
     const size_t rings = (4 * (size_t)P->sweep * (P->Tx + 2) + 1) * P->n_sub * P->Ew * 16;
-    P->lds_bytes = std::max(rings, (size_t)P->block * 2 * P->NC * sizeof(double));
+    P->lds_bytes = std::max(rings, flush_bytes);
     P->sweep_fn = sweep_kernel_fn(P->prec, P->kind, P->sweep, P->has_onsite, P->has_mask, P->has_phase, P->block,
                                   P->Tx, P->Ew);
-  } else {
-    P->lds_bytes = (P->variant == 2) ? ring_bytes : (size_t)P->block * 2 * P->NC * sizeof(double);
   }
-  P->step_fn = (P->prec == KPM_FP32)
-                   ? pick_step_kind<float, false>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase)
-                   : pick_step_kind<double, false>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase);
-  P->step_fn_vel = (P->prec == KPM_FP32)
-                       ? pick_step_kind<float, true>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase)
-                       : pick_step_kind<double, true>(P->kind, P->variant, P->has_onsite, P->has_mask, P->has_phase);
   if (const char* lg = std::getenv("KPM_LOG"); lg && *lg && std::strcmp(lg, "0") != 0) {
     static const char* kKind[] = {"honeycomb", "honeycomb+spin", "square"};
     std::fprintf(stderr,

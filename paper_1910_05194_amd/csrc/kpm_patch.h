@@ -15,7 +15,7 @@
 // instead, (PX + 2 KS)(PY + 2 KS) for PX PY.  Per step (us), before -> patches:
 // honeycomb 64 x 64, 4 vectors, FP64 4.08 -> 1.5; 128 x 128, 4, FP32 4.95 -> 1.9;
 // square 273 x 197, 8, FP64 5.5 -> 4.0; spinful 64 x 64, 4, FP32 5.7 -> 2.2;
-// 235 x 231 12.7 -> 6.7; spinful 512 x 512, 8 vectors would be 45 -> 52 (rows stay).
+// 164 x 142, 2 7.1 -> 2.8; 512 x 512, 8 vectors would be 35 -> 52 (rows stay).
 // Workgroups of 1024 threads with half the sites each: 5 to 15 % slower.
 //
 // Items: one site's chunk (both spins).  Item i = cell * (NSUB Ew) + s Ew + cl is

@@ -13,12 +13,13 @@ void* patch_fn_f64(int kind, bool phase, int spt, bool hist);
 // launches (us), honeycomb FP32, one patch per CU: 1 site per thread 7.1 (4 steps),
 // 8.0 (6); 2 sites 9.4 (8); 4 sites 9.6 (4), 12.6 (8); 4 sites and 8 steps with 2 and
 // 3.3 patches per CU 25 and 36.  FP64 with phases takes 1.8 times as much per patch,
-// a spin 1.7 in FP32 and 3 in FP64.
-static double patch_time(const kpm_plan* P, int spt, int ks, int n) {
+// a spin 1.7 in FP32 and 3 in FP64.  mem_us: the vectors in and out, not hidden in a
+// launch of one or two rounds.
+static double patch_time(const kpm_plan* P, int spt, int ks, int n, double mem_us) {
   double g = P->n_spin == 2 ? 1.7 : 1.0;
   if (P->prec == KPM_FP64) g *= P->n_spin == 2 ? 1.8 : 1.1;
   if (P->has_phase) g *= P->prec == KPM_FP64 && P->n_spin == 1 ? 1.7 : 1.2;
-  return (5.0 + n * g * (0.6 * spt + ks * (0.35 + 0.1 * spt))) / ks;
+  return (5.0 + mem_us + n * g * (0.6 * spt + ks * (0.35 + 0.1 * spt))) / ks;
 }
 
 bool patch_shape(const kpm_plan* P, bool hist, int max_steps, int lds_max, int n_cu, PatchShape* best) {
@@ -34,6 +35,7 @@ bool patch_shape(const kpm_plan* P, bool hist, int max_steps, int lds_max, int n
   }
   const int max_tiles = std::min(2048, kPatchRounds * n_cu);
   double best_t = 1e30;
+  const double vec_us = (double)P->n_orb * P->Rp * 2 * P->tsize / 5.0e6;
   const int ks_max = std::min(max_steps, patch_steps(P->kind));
   for (int lgw = 0; lgw <= 3 && (1 << lgw) < 2 * P->E; ++lgw) {
     const int n_rg = (int)ceil_div(P->E, 1 << lgw);
@@ -50,7 +52,9 @@ bool patch_shape(const kpm_plan* P, bool hist, int max_steps, int lds_max, int n
           int64_t tiles = 0;
           for (int l = 0; l < n_lat; ++l) tiles += n_rg * ceil_div(P->lats[l].L1, px) * ceil_div(P->lats[l].L2, py);
           if (tiles > max_tiles) continue;
-          const double t = patch_time(P, spt, ks, (int)ceil_div(tiles, n_cu));
+          // Two vectors come in with their halos, two (or one per step) go out, at 5 TB/s.
+          const double mem_us = vec_us * (2.0 * (double)tiles * ex * (py + 2 * ks) / (cells * n_rg) + (hist ? ks : 2));
+          const double t = patch_time(P, spt, ks, (int)ceil_div(tiles, n_cu), mem_us);
           if (t < best_t) {
             best_t = t;
             best->px = px;

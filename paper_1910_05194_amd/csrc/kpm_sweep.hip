@@ -550,7 +550,7 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
   const kpm_lattice_t& L = P->lats[0];
   const int ks = kHistSteps;
   const double vec_b = (double)P->n_orb * P->Rp * 2 * P->tsize;
-  double us = 4.6 + 3.0 * vec_b / 4.8e6;   // single steps, as for the density of states
+  double us = 4.2 + 3.0 * vec_b / 6.0e6;   // single steps, as for the density of states
   // Row sweeps without a spin; the kernel addresses a lattice row with 32-bit byte offsets.
   const bool rows = P->n_spin == 1 && (int64_t)L.L1 * P->n_sub * P->Rp * 2 * (int64_t)P->tsize < (int64_t(1) << 31);
   // Up to 8 chunks (128 bytes) of each site, fewer where the workgroup would span
@@ -575,9 +575,7 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
     conc = (int64_t)n_cu * std::max(1, std::min(kMaxStepBlock / block, (int)(lds_max / H->lds_bytes)));
     us = sweep_rows(P->lats, ks, xstep, n_rg, conc, &ty);
   }
-  // A launch writes as many vectors as it makes steps: at 5 TB/s on top.
-  if (patch_shape(P, true, max_levels, lds_max, n_cu, &H->patch) &&
-      H->patch.us_per_step + (block >= 64 ? 0.5 * vec_b / 5.0e6 : 0.0) < kPatchGain * us) {
+  if (patch_shape(P, true, max_levels, lds_max, n_cu, &H->patch) && H->patch.us_per_step < kPatchGain * us) {
     block = kPatchBlock;
     ew = 1 << H->patch.lgw;
     n_rg = (int)ceil_div(P->E, ew);
