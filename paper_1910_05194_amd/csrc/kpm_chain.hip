@@ -599,8 +599,6 @@ int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, Cha
   }
   const int xstep = tx - 2 * (ks - 1);
   const int n_rg = (int)ceil_div(P->E, ew);
-  // Rows per tile: the fewest rounds of concurrent workgroups, each round costing the tile's
-  // rows plus the 3 (KS - 1) iterations of its skewed start and drain.
   int n_cu = 256;
   {
     int dev = 0, v = 0;
@@ -610,18 +608,11 @@ int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, Cha
   }
   const int per_cu = std::max(1, std::min(kMaxStepBlock * 4 / block, (int)(lds_max / lds)));
   const int64_t conc = (int64_t)n_cu * per_cu;
+  // Rows per tile as for the other sweeps.  A choice among 8, 16, 32, 48, ... rows left a
+  // spinful 512 x 512 lattice (2 vectors) 160 tiles of 28 rows of work for 256 CUs (58 us a sweep,
+  // now 48), and a honeycomb 128 x 128 one (2, FP64) 32 tiles of 12 (16 us, now 8.8).
   int best_ty = rows;
-  double best_cost = 1e300;
-  for (int ty : {256, 192, 128, 96, 64, 48, 32, 16, 8}) {
-    if (rows > 0) break;   // rows given
-    const int64_t nt = (int64_t)n_rg * ceil_div(L.L2, ty) * ceil_div(L.L1, xstep);
-    const int64_t rounds = ceil_div(nt, conc);
-    const double cost = (double)rounds * (double)(ceil_div(std::min(ty, L.L2) + 3 * (ks - 1), 4) * 4);
-    if (cost < best_cost * 0.999) {
-      best_cost = cost;
-      best_ty = ty;
-    }
-  }
+  if (rows <= 0) (void)sweep_rows(P->lats, ks, xstep, n_rg, conc, &best_ty);
   std::vector<int4> tiles;
   for (int g = 0; g < n_rg; ++g)
     for (int y0 = 0; y0 < L.L2; y0 += best_ty)
