@@ -240,44 +240,104 @@ __global__ void __launch_bounds__(512) gamma_bf16_kernel(const __bf16* __restric
       }
 }
 
-// FP64 reference GEMM (exact mode): 16 x 16 output tile per workgroup, k tiles
-// of 16 complex values staged in LDS; grid.z splits K.
+// FP64 GEMM (exact mode) on the FP64 matrix cores: per output element the complex sum
+// conj(L_nk) R_mk over one K chunk.  A workgroup forms a 32 x 32 tile; its four waves
+// take a quarter of every K block each (64 complex values) and meet in LDS at the end.
+// One 16 x 16 x 4 product covers four complex values of one part, lane l holding row
+// (column) l % 16 and value l / 16, so a lane's 16-byte load feeds the real and the
+// imaginary products and nothing is staged: the loads come from L1 and L2 (16 bytes a
+// clock and CU at the full matrix rate), two steps ahead of their use.  Workgroup b
+// runs on XCD b % 8; all tiles of a K chunk share an XCD, so its rows leave HBM once.
+// The bound is the matrix rate (71 TF/s for a large product).  M = 128, K = 65536:
+// 389 us with 16 x 16 tiles of scalar FMAs from LDS, now 163 (53 TF/s).
 template <typename T>
-__global__ void __launch_bounds__(256) gamma_fp64_kernel(const T* __restrict__ L, const T* __restrict__ R, int M,
-                                                         int Mp, int64_t Kc, int64_t kchunk, double* __restrict__ part) {
-  __shared__ double ls[16][17][2], rs[16][17][2];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int n0 = blockIdx.y * 16, m0 = blockIdx.x * 16;
-  const int64_t k_begin = (int64_t)blockIdx.z * kchunk;
-  const int64_t k_end = min(Kc, k_begin + kchunk);
-  double ar = 0.0, ai = 0.0;
-  for (int64_t k0 = k_begin; k0 < k_end; k0 += 16) {
-    // thread (ty, tx) stages L[n0+ty][k0+tx] and R[m0+ty][k0+tx]; k0 is a multiple
-    // of 16 and kBlkK of 16, so k0 + tx lies in K block k0 / kBlkK.
-    const int64_t kb = (k0 / kBlkK) * (int64_t)Mp;
-    const int64_t kq = k0 % kBlkK + tx;
-    const int n = n0 + ty, m = m0 + ty;
-    const bool kin = k0 + tx < k_end;
-    const int64_t li = 2 * ((kb + n) * kBlkK + kq), ri = 2 * ((kb + m) * kBlkK + kq);
-    ls[ty][tx][0] = (kin && n < M) ? (double)L[li] : 0.0;
-    ls[ty][tx][1] = (kin && n < M) ? (double)L[li + 1] : 0.0;
-    rs[ty][tx][0] = (kin && m < M) ? (double)R[ri] : 0.0;
-    rs[ty][tx][1] = (kin && m < M) ? (double)R[ri + 1] : 0.0;
-    __syncthreads();
+__global__ void __launch_bounds__(256, 2) gamma_fp64_kernel(const T* __restrict__ L, const T* __restrict__ R, int M,
+                                                            int Mp, int n_blocks, int chunk, int ks_used,
+                                                            double* __restrict__ part) {
+  typedef T v2 __attribute__((ext_vector_type(2)));
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  __shared__ f64x2 red[4][32][32];
+  const int nt = (M + 31) / 32;
+  const int job = (int)(blockIdx.x >> 3);
+  const int ks = (int)(blockIdx.x & 7) + 8 * (job / (nt * nt));
+  if (ks >= ks_used) return;
+  const int tile = job % (nt * nt);
+  const int n0 = tile / nt * 32, m0 = tile % nt * 32;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int kb0 = ks * chunk, kb1 = min(n_blocks, kb0 + chunk);
+  // Rows beyond M repeat row M - 1; their results are not stored.
+  const T* p[4];
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const double lr = ls[ty][kk][0], li = ls[ty][kk][1];
-      const double rr = rs[tx][kk][0], ri = rs[tx][kk][1];
-      ar += lr * rr + li * ri;
-      ai += lr * ri - li * rr;
-    }
-    __syncthreads();
+  for (int i = 0; i < 2; ++i) {
+    p[i] = L + 2 * (((int64_t)kb0 * Mp + min(n0 + 16 * i + r16, M - 1)) * kBlkK + 64 * wave + g);
+    p[2 + i] = R + 2 * (((int64_t)kb0 * Mp + min(m0 + 16 * i + r16, M - 1)) * kBlkK + 64 * wave + g);
   }
-  const int n = n0 + ty, m = m0 + tx;
-  if (n < M && m < M) {
-    double* pb = part + (int64_t)blockIdx.z * M * M * 2;
-    pb[((int64_t)n * M + m) * 2] = ar;
-    pb[((int64_t)n * M + m) * 2 + 1] = ai;
+  const int64_t block_elems = (int64_t)Mp * kBlkK * 2;
+  f64x4 re[2][2], im[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) re[i][j] = im[i][j] = f64x4{};
+  v2 buf[2][2][4];   // [set][step][operand]
+  auto load = [&](v2 (&b)[2][4], int st) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int o = 0; o < 4; ++o) b[q][o] = *reinterpret_cast<const v2*>(p[o] + 8 * (st + q));
+  };
+  auto multiply = [&](const v2 (&b)[2][4]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      f64x2 x[4];
+#pragma unroll
+      for (int o = 0; o < 4; ++o) x[o] = f64x2{(double)b[q][o][0], (double)b[q][o][1]};
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i][0], x[2 + j][0], re[i][j], 0, 0, 0);
+          im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i][0], x[2 + j][1], im[i][j], 0, 0, 0);
+        }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i][1], x[2 + j][1], re[i][j], 0, 0, 0);
+          im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i][1], -x[2 + j][0], im[i][j], 0, 0, 0);
+        }
+    }
+  };
+  if (kb0 < kb1) load(buf[0], 0);
+  for (int kb = kb0; kb < kb1; ++kb) {
+#pragma unroll
+    for (int st = 0; st < 16; st += 4) {
+      load(buf[1], st + 2);
+      multiply(buf[0]);
+      if (st + 4 < 16) {
+        load(buf[0], st + 4);
+      } else if (kb + 1 < kb1) {
+#pragma unroll
+        for (int o = 0; o < 4; ++o) p[o] += block_elems;
+        load(buf[0], 0);
+      }
+      multiply(buf[1]);
+    }
+  }
+  // A 16 x 16 result: lane l, element e holds row 4 e + l / 16, column l % 16.
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[wave][16 * i + 4 * e + g][16 * j + r16] = f64x2{re[i][j][e], im[i][j][e]};
+  __syncthreads();
+  double* pb = part + (int64_t)ks * M * M * 2;
+  for (int q = threadIdx.x; q < 32 * 32; q += 256) {
+    const int a = q >> 5, b = q & 31;
+    const f64x2 t = (red[0][a][b] + red[1][a][b]) + (red[2][a][b] + red[3][a][b]);
+    if (n0 + a < M && m0 + b < M) *reinterpret_cast<f64x2*>(pb + ((int64_t)(n0 + a) * M + m0 + b) * 2) = t;
   }
 }
 
@@ -310,10 +370,12 @@ hipError_t gamma_accumulate_bf16(const __bf16* Lh, const __bf16* Ll, const __bf1
 template <typename T>
 hipError_t gamma_accumulate_fp64(const T* L, const T* R, int M, int Mp, int64_t Kc, int KS, double* part,
                                  double* acc, hipStream_t s) {
-  const int64_t kchunk = ceil_div(ceil_div(Kc, KS), 16) * 16;
-  const int ks_used = (int)ceil_div(Kc, kchunk);
-  dim3 grid((unsigned)ceil_div(M, 16), (unsigned)ceil_div(M, 16), (unsigned)ks_used);
-  hipLaunchKernelGGL(gamma_fp64_kernel<T>, grid, dim3(256), 0, s, L, R, M, Mp, Kc, kchunk, part);
+  if (Kc % kBlkK != 0 || Mp < M) return hipErrorInvalidValue;
+  const int n_blocks = (int)(Kc / kBlkK), nt = (int)ceil_div(M, 32);
+  const int chunk = (int)ceil_div(n_blocks, KS);
+  const int ks_used = (int)ceil_div(n_blocks, chunk);
+  const int grid = (int)(ceil_div(ks_used, 8) * 8) * nt * nt;
+  hipLaunchKernelGGL(gamma_fp64_kernel<T>, dim3(grid), dim3(256), 0, s, L, R, M, Mp, n_blocks, chunk, ks_used, part);
   const int64_t n = (int64_t)M * M * 2;
   hipLaunchKernelGGL(gamma_reduce_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, part, ks_used, n, acc);
   return ::kpm::launch_status();
