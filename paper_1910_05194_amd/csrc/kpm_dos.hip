@@ -1240,8 +1240,10 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
     }
   }
   // Patches where the library chooses the whole shape and the model sees a clear gain.
+  // They need four vectors as the sweeps do; in a caller's arena the single-step kernels
+  // keep their two, so that no workload outgrows it.
   const bool shape_given = tune && (tune->block > 0 || tune->rows > 0 || tune->grid > 0 || tune->kernel > 0 || tune->chunks > 0);
-  if (!shape_given && room && patch_shape(P, false, patch_steps(P->kind), lds_max, n_cu, &P->patch_sh) &&
+  if (!shape_given && room && (!P->use_arena || P->variant >= 3) && patch_shape(P, false, patch_steps(P->kind), lds_max, n_cu, &P->patch_sh) &&
       P->patch_sh.us_per_step < kPatchGain * us_per_step) {
     P->patch = true;
     P->sweep = P->patch_sh.ks;
@@ -1314,11 +1316,13 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
   // Moment partials: at most 2 GB, or an eighth of a caller-provided arena.
   const double budget = P->use_arena ? (double)P->arena_cap / 8.0 : 2.0e9;
   P->steps_per_chunk = (int)std::max<double>(1.0, std::min<double>(P->n_steps, std::floor(budget / part_step_bytes)));
-  // A sweep kernel writes the partials of its KS steps into one chunk.
-  if (P->sweep > 1)
-    P->steps_per_chunk = P->steps_per_chunk == P->n_steps
-                             ? (int)ceil_div(P->n_steps, P->sweep) * P->sweep
+  // A launch writes the partials of its KS steps into one chunk.
+  if (P->sweep > 1) {
+    const int all = (int)ceil_div(P->n_steps, P->sweep) * P->sweep;
+    P->steps_per_chunk = all * part_step_bytes <= budget
+                             ? all
                              : std::max(P->sweep, P->steps_per_chunk - P->steps_per_chunk % P->sweep);
+  }
 
   // Algorithmic bytes per step: read v_n and v_{n-1}, write v_{n+1}, per-site
   // arrays; a sweep kernel reads two vectors and the site arrays and writes
