@@ -29,7 +29,7 @@
 // branch on the column); stores and block stores are the only divergent
 // branches.
 
-#include "kpm_stencil.h"
+#include "kpm_chain.h"
 
 #include <type_traits>
 
@@ -56,85 +56,6 @@ struct ChainArgs {
   int read_w1, nlev, vdir, has_onsite, has_mask, has_phase;
   int Tx, Ty, E, Ew, Rp;
 };
-
-// Hopping coefficients of one thread's orbital (per tile): the complex
-// coefficient of the value of neighbour k, spin s2, in the result for the
-// thread's spin, Peierls phase and hopping folded in.  Spinless: hop *
-// exp(i theta_k).  Spinful: exp(i theta_k) times the 2 x 2 Rashba block
-// entry, B_k[sp][s2] on sublattice A and conj(B_k[s2][sp]) on sublattice B.
-template <typename T, int KIND>
-struct Coef {
-  static constexpr int NNB = KindTraits<KIND>::NNB, NSPIN = KindTraits<KIND>::NSPIN;
-  T re[NNB][NSPIN], im[NNB][NSPIN];
-  T vc[NNB];   // velocity weights (mode 1)
-};
-
-// One orbital: out = a (H~ v) - b w and, in mode 1, the velocity stencil of
-// v, vout = vel_scale sum_k d_k term_k, where term_k is the hop from
-// neighbour k (both spins) applied to its values.
-template <typename T, int KIND, int MODE>
-__device__ inline void chain_site(T a, T b, bool read_w, const Coef<T, KIND>& C, T ons, T vel_scale, bool alive,
-                                  const Pack<T>& vo, const Pack<T>& wo,
-                                  const Pack<T> (&vn)[KindTraits<KIND>::NNB][KindTraits<KIND>::NSPIN], Pack<T>& out,
-                                  Pack<T>& vout) {
-  constexpr int NC = Pack<T>::NC;
-  constexpr int NSPIN = KindTraits<KIND>::NSPIN;
-  constexpr int NNB = KindTraits<KIND>::NNB;
-#pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    T hr = ons * vo.v[2 * j], hi = ons * vo.v[2 * j + 1];
-    T gr = 0, gi = 0;
-    // Complex products as chains of FMAs (the compiler may not reassociate
-    // a sum of products into them): four per coefficient and value.  Mode 0
-    // adds every term straight into the result; mode 1 keeps each
-    // neighbour's term for the velocity sum.
-#pragma unroll
-    for (int k = 0; k < NNB; ++k) {
-      if constexpr (MODE == 1) {
-        T tr = C.re[k][0] * vn[k][0].v[2 * j];
-        T ti = C.re[k][0] * vn[k][0].v[2 * j + 1];
-        tr = fma(-C.im[k][0], vn[k][0].v[2 * j + 1], tr);
-        ti = fma(C.im[k][0], vn[k][0].v[2 * j], ti);
-#pragma unroll
-        for (int s2 = 1; s2 < NSPIN; ++s2) {
-          tr = fma(C.re[k][s2], vn[k][s2].v[2 * j], tr);
-          tr = fma(-C.im[k][s2], vn[k][s2].v[2 * j + 1], tr);
-          ti = fma(C.re[k][s2], vn[k][s2].v[2 * j + 1], ti);
-          ti = fma(C.im[k][s2], vn[k][s2].v[2 * j], ti);
-        }
-        hr += tr;
-        hi += ti;
-        gr = fma(C.vc[k], tr, gr);
-        gi = fma(C.vc[k], ti, gi);
-      } else {
-#pragma unroll
-        for (int s2 = 0; s2 < NSPIN; ++s2) {
-          hr = fma(C.re[k][s2], vn[k][s2].v[2 * j], hr);
-          hr = fma(-C.im[k][s2], vn[k][s2].v[2 * j + 1], hr);
-          hi = fma(C.re[k][s2], vn[k][s2].v[2 * j + 1], hi);
-          hi = fma(C.im[k][s2], vn[k][s2].v[2 * j], hi);
-        }
-      }
-    }
-    T orr = a * hr, oi = a * hi;
-    if (read_w) {
-      orr -= b * wo.v[2 * j];
-      oi -= b * wo.v[2 * j + 1];
-    }
-    if (!alive) {
-      orr = 0;
-      oi = 0;
-      gr = 0;
-      gi = 0;
-    }
-    out.v[2 * j] = orr;
-    out.v[2 * j + 1] = oi;
-    if constexpr (MODE == 1) {
-      vout.v[2 * j] = vel_scale * gr;
-      vout.v[2 * j + 1] = vel_scale * gi;
-    }
-  }
-}
 
 // Threads: tid = ((column * NSUB + sub) * NSPIN + spin) * Ew + chunk; each
 // thread forms one orbital (one spin of one site) and reads both spins of its
@@ -556,6 +477,8 @@ namespace kpm {
 
 int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, ChainPlan* C) {
   *C = ChainPlan();
+  const bool free_shape = ks == 0 && rows == 0;
+  if (ks == 0) ks = P->n_spin == 2 ? 4 : 2;
   KPM_CHECK_ARG(ks >= 2 && ks <= 4, "chain sweep: 2..4 steps per sweep");
   KPM_CHECK_ARG(P->n_lat == 1, "chain sweep: one lattice per plan");
   // The spinful FP64 kernel spills registers at four steps per sweep.
@@ -612,11 +535,25 @@ int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, Cha
   // spinful 512 x 512 lattice (2 vectors) 160 tiles of 28 rows of work for 256 CUs (58 us a sweep,
   // now 48), and a honeycomb 128 x 128 one (2, FP64) 32 tiles of 12 (16 us, now 8.8).
   int best_ty = rows;
-  if (rows <= 0) (void)sweep_rows(P->lats, ks, xstep, n_rg, conc, &best_ty);
+  double us_per_step = 0.0;
+  if (rows <= 0) us_per_step = sweep_rows(P->lats, ks, xstep, n_rg, conc, &best_ty);
   std::vector<int4> tiles;
-  for (int g = 0; g < n_rg; ++g)
-    for (int y0 = 0; y0 < L.L2; y0 += best_ty)
-      for (int x0 = 0; x0 < L.L1; x0 += xstep) tiles.push_back(make_int4(0, g, x0, y0));
+  // Small spinless lattices run on patches, where the model sees a clear gain: 128 x 128,
+  // 2 vectors, FP64: 1.61 -> 1.01 ms for all moments of order 128.  A spinful site's 2 x 2
+  // blocks with phases would need 24 coefficients per item: rows.
+  if (free_shape && P->n_spin == 1 && patch_shape(P, true, kPatchSteps, lds_max, n_cu, &C->patch) &&
+      C->patch.us_per_step < kPatchGain * us_per_step) {
+    const PatchShape& S = C->patch;
+    ks = S.ks;
+    for (int y0 = 0; y0 < L.L2; y0 += S.py)
+      for (int x0 = 0; x0 < L.L1; x0 += S.px)
+        for (int g = 0; g < (int)ceil_div(P->E, 1 << S.lgw); ++g) tiles.push_back(make_int4(0, g, x0, y0));
+  } else {
+    C->patch = PatchShape();
+    for (int g = 0; g < n_rg; ++g)
+      for (int y0 = 0; y0 < L.L2; y0 += best_ty)
+        for (int x0 = 0; x0 < L.L1; x0 += xstep) tiles.push_back(make_int4(0, g, x0, y0));
+  }
   C->ks = ks;
   C->block = block;
   C->Tx = tx;
@@ -626,7 +563,9 @@ int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, Cha
   C->n_tiles = (int)tiles.size();
   C->grid = (int)(ceil_div(std::min<int64_t>((int64_t)tiles.size(), conc), 8) * 8);
   for (int m = 0; m < 2; ++m)
-    for (int sp = 0; sp < 2; ++sp) C->fn[m][sp] = chain_kernel_fn(P->prec, P->kind, ks, m, sp == 1);
+    for (int sp = 0; sp < 2; ++sp)
+      C->fn[m][sp] = C->patch.ks ? patch_chain_fn(P->prec, P->kind, C->patch.spt, m, sp == 1)
+                                 : chain_kernel_fn(P->prec, P->kind, ks, m, sp == 1);
   const size_t vec_bytes = (size_t)P->n_orb * P->Rp * 2 * P->tsize;
   hipError_t e = dev_malloc(&C->tiles, tiles.size() * sizeof(int4));
   if (e == hipSuccess) e = dev_malloc(&C->Z, vec_bytes);
@@ -654,6 +593,8 @@ template <typename T>
 static hipError_t chain_launch(const kpm_plan* P, const ChainPlan& C, hipStream_t s, int mode, const void* v,
                                const void* w, void* out_a, void* out_b, bool first, int nlev, void* blk, void* blk_lo,
                                int64_t row0, int64_t blk_rows, int vdir, double vel_scale) {
+  if (C.patch.ks)
+    return patch_chain_run(P, C, s, mode, v, w, out_a, out_b, first, nlev, blk, blk_lo, row0, blk_rows, vdir, vel_scale);
   ChainArgs<T> a;
   a.lats = (const LatDev<T>*)P->latdev;
   a.tiles = C.tiles;

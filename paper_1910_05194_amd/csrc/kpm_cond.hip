@@ -135,15 +135,15 @@ static int cond_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double
   // Multi-step chain sweeps: KS = 4 steps per launch on the spinful lattice
   // (3 in FP64), 2 on the spinless ones (the fastest measured on 1024^2
   // lattices; the spinless kernels are bound by instruction issue at larger
-  // KS).  KPM_CHAIN_STEPS=1 keeps single steps, 2..4 sets KS; KPM_CHAIN_ROWS
-  // sets the rows per tile.  Without a tile shape that fits, single steps.
+  // KS), or patches of small spinless lattices.  KPM_CHAIN_STEPS=1 keeps single
+  // steps, 2..4 sets row sweeps of KS; KPM_CHAIN_ROWS sets the rows per tile.  Without a tile shape that fits, single steps.
   ChainPlan C;
   bool sweep_chains = false;
   if (st == KPM_OK) {
-    int ks = (P->n_spin == 2) ? 4 : 2, rows = 0;
-    if (const char* cs = std::getenv("KPM_CHAIN_STEPS"); cs && *cs) ks = std::atoi(cs);
+    int ks = 0, rows = 0;   // 0: the library's choice
+    if (const char* cs = std::getenv("KPM_CHAIN_STEPS"); cs && *cs) ks = std::max(1, std::atoi(cs));
     if (const char* cr = std::getenv("KPM_CHAIN_ROWS"); cr && *cr) rows = std::max(0, std::atoi(cr));
-    if (ks >= 2) {
+    if (ks == 0 || ks >= 2) {
       const int cst = chain_plan_create(P, std::min(ks, 4), rows, Mp, &C);
       if (cst == KPM_OK) sweep_chains = true;
       else if (cst == KPM_E_UNSUPPORTED) clear_error();   // single steps
