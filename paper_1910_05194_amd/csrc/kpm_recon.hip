@@ -583,7 +583,8 @@ __global__ void __launch_bounds__(256) series_gemm_kernel(const double* __restri
       const int ql = g.q0 + i0 + rowl;
       if (i0 + rowl < g.nq) {
         const int q = side ? g.Q - 1 - ql : ql;
-        out.part[(int64_t)blockIdx.x * g.Q + q] = red[0][side][rowl] + red[1][side][rowl];
+        // (The middle cell of an odd Q is its own partner and has one writer, side 0.)
+        if (side == 0 || q != ql) out.part[(int64_t)blockIdx.x * g.Q + q] = red[0][side][rowl] + red[1][side][rowl];
       }
     }
   }
@@ -817,7 +818,7 @@ __global__ void __launch_bounds__(1024) optical_rank1_kernel(const double* __res
       for (int x = 0; x < 4; ++x) s[x] += red[w][lane][x];
     const int q = g.q0 + i;
     x1[q] = make_double2(s[0] + s[2], s[1] + s[3]);
-    x1[g.Q - 1 - q] = make_double2(s[0] - s[2], s[1] - s[3]);
+    if (g.Q - 1 - q != q) x1[g.Q - 1 - q] = make_double2(s[0] - s[2], s[1] - s[3]);
   }
 }
 
@@ -833,6 +834,7 @@ __global__ void __launch_bounds__(256) optical_para_kernel(const double* __restr
   if (row >= 2 * (int64_t)g.nq) return;
   const int ql = g.q0 + (int)(row >> 1);
   const int q = (row & 1) ? g.Q - 1 - ql : ql;
+  if ((row & 1) && q == ql) return;   // the middle cell of an odd Q: row 0 of its pair alone
   const int k0 = blockIdx.y * kOptK;
   const double eps = cospi((q + 0.5) / g.Q);
   cplx pw[kOptK][2], st[kOptK][2], sum[kOptK][2], pre[kOptK][2];   // [frequency][retarded at +w, advanced at -w]
