@@ -9,7 +9,10 @@
 // are therefore kept for later calls, within these bounds:
 // - per device, idle blocks take at most an eighth of its memory, and a block is
 //   kept only while at least as much as all idle blocks stays free for others;
-//   the oldest go first;
+//   the oldest go first.  Every release is held against the bound; the free memory
+//   in it is read again after each 16 MB released (the query takes longer than the
+//   rest of a small release);
+// - per device, at most 1024 idle blocks (a request looks at each);
 // - an allocation that fails gives every idle block back and tries once more;
 // - kpm_release_workspace() gives them back on request;
 // - a block serves a request only if it is at most an eighth larger (or 64 KB).
@@ -30,11 +33,21 @@ namespace kpm {
 
 namespace {
 
+constexpr size_t kLookEvery = size_t(16) << 20;
+constexpr size_t kMaxIdle = 1024;
+
 struct Block {
   void* p;
   size_t cap;
   int dev;
   uint64_t freed;   // release count when it became idle
+};
+
+// The idle blocks of one device.
+struct Idle {
+  size_t bytes = 0, count = 0;
+  size_t bound = 0;                          // on bytes, from the last look at the device's memory
+  size_t unseen = kLookEvery;                // bytes released since
 };
 
 struct Pool {
@@ -43,6 +56,7 @@ struct Pool {
   std::list<Block> idle;                        // oldest first
   uint64_t releases = 0;
   std::unordered_map<int, uint64_t> synced;     // per device: release count before its last synchronisation
+  std::unordered_map<int, Idle> idle_of;
 };
 
 // Never destroyed: objects with static lifetime may still release memory at exit.
@@ -56,25 +70,26 @@ size_t round_up(size_t bytes) {
   return (std::max<size_t>(bytes, 1) + g - 1) / g * g;
 }
 
-size_t idle_bytes(const Pool& P, int dev) {
-  size_t n = 0;
-  for (const Block& b : P.idle)
-    if (b.dev == dev) n += b.cap;
-  return n;
+std::list<Block>::iterator drop(Pool& P, std::list<Block>::iterator it) {
+  Idle& d = P.idle_of[it->dev];
+  d.bytes -= it->cap;
+  d.count -= 1;
+  return P.idle.erase(it);
 }
 
-// Gives back idle blocks of a device, oldest first, until at most keep bytes are left.
-size_t trim(Pool& P, int dev, size_t keep) {
-  size_t have = idle_bytes(P, dev), gone = 0;
-  for (auto it = P.idle.begin(); it != P.idle.end() && have > keep;) {
+// Gives back idle blocks of a device, oldest first, until at most keep bytes and
+// count blocks are left.
+size_t trim(Pool& P, int dev, size_t keep, size_t count) {
+  const Idle& d = P.idle_of[dev];
+  size_t gone = 0;
+  for (auto it = P.idle.begin(); it != P.idle.end() && (d.bytes > keep || d.count > count);) {
     if (it->dev != dev) {
       ++it;
       continue;
     }
-    have -= it->cap;
     gone += it->cap;
     (void)hipFree(it->p);
-    it = P.idle.erase(it);
+    it = drop(P, it);
   }
   return gone;
 }
@@ -105,12 +120,12 @@ hipError_t pool_malloc(void** out, size_t bytes) {
       }
       P.used.emplace(best->p, *best);
       *out = best->p;
-      P.idle.erase(best);
+      drop(P, best);
       return hipSuccess;
     }
     void* p = nullptr;
     e = hipMalloc(&p, need);
-    if (e == hipErrorOutOfMemory && trim(P, dev, 0) > 0) {
+    if (e == hipErrorOutOfMemory && trim(P, dev, 0, 0) > 0) {
       (void)hipGetLastError();
       e = hipMalloc(&p, need);
     }
@@ -137,20 +152,26 @@ hipError_t pool_free(void* p) {
     Block b = it->second;
     P.used.erase(it);
     int cur = 0;
-    size_t free_b = 0, total_b = 0;
     bool keep = hipGetDevice(&cur) == hipSuccess && cur == b.dev;   // (another device's limits are not at hand)
-    if (keep && b.cap >= (size_t(16) << 20)) {
-      keep = hipMemGetInfo(&free_b, &total_b) == hipSuccess && b.cap <= total_b / 8;
-      if (keep) {
-        const size_t bound = std::min(total_b / 8, free_b);
-        trim(P, b.dev, bound > b.cap ? bound - b.cap : 0);
-        keep = b.cap <= bound;
+    if (keep) {
+      Idle& d = P.idle_of[b.dev];
+      d.unseen += b.cap;
+      if (d.unseen >= kLookEvery) {
+        size_t free_b = 0, total_b = 0;
+        keep = hipMemGetInfo(&free_b, &total_b) == hipSuccess;
+        d.bound = keep ? std::min(total_b / 8, free_b) : 0;
+        d.unseen = keep ? 0 : kLookEvery;
       }
+      keep = keep && b.cap <= d.bound;
+      trim(P, b.dev, keep ? d.bound - b.cap : d.bound, kMaxIdle - 1);
     }
     if (keep) {
       b.freed = ++P.releases;
       try {
+        Idle& d = P.idle_of[b.dev];
         P.idle.push_back(b);
+        d.bytes += b.cap;
+        d.count += 1;
         return hipSuccess;
       } catch (...) {
       }
@@ -165,11 +186,10 @@ size_t pool_release() {
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
   size_t n = 0;
-  for (const Block& b : P.idle) {
-    n += b.cap;
-    (void)hipFree(b.p);
+  for (auto it = P.idle.begin(); it != P.idle.end(); it = drop(P, it)) {
+    n += it->cap;
+    (void)hipFree(it->p);
   }
-  P.idle.clear();
   return n;
 }
 
@@ -180,7 +200,8 @@ hipError_t mem_available(size_t* free_bytes, size_t* total_bytes) {
   if (e != hipSuccess) return e;
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
-  *free_bytes += idle_bytes(P, dev);
+  const auto it = P.idle_of.find(dev);
+  if (it != P.idle_of.end()) *free_bytes += it->second.bytes;
   return hipSuccess;
 }
 
