@@ -1254,15 +1254,23 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
     P->Ty = P->patch_sh.py;
   }
 
-  // Tile work list ordered (lattice, r-group, row band, column band); patches with
-  // the r-groups innermost: the chunks of one site share cache lines, and the
-  // workgroups of neighbouring tiles an L2.
+  // Tile work list ordered (lattice, r-group, row band, column band), or with the
+  // r-groups innermost: on patches, and in the sweeps where a site's chunks are not
+  // whole 128-byte lines.  The groups then share lines, and the workgroups of
+  // neighbouring tiles an L2 (13 chunks on 1000 x 1000, four steps per sweep: 199 us a
+  // step with the groups apart, 110 with them together; 16 chunks: 107.5 and 109.6).
+  // Each tile of a workgroup that then changes the group takes a slot of its own, so
+  // the lists of small tiles (and all but one tile per workgroup in a caller's arena)
+  // stay apart.
+  int64_t n_all = 0;
+  for (int l = 0; l < n_lat; ++l) n_all += ceil_div(lat[l].L1, xstep) * P->n_rg * ceil_div(lat[l].L2, P->Ty);
+  const bool inner_g = P->patch || (P->variant >= 3 && P->E % 8 != 0 && n_all <= (P->use_arena ? 2048 : 65536));
   std::vector<int4> tiles;
   for (int l = 0; l < n_lat; ++l)
-    for (int go = 0; go < (P->patch ? 1 : P->n_rg); ++go)
+    for (int go = 0; go < (inner_g ? 1 : P->n_rg); ++go)
       for (int y0 = 0; y0 < lat[l].L2; y0 += P->Ty)
         for (int x0 = 0; x0 < lat[l].L1; x0 += xstep)
-          for (int g = go; g < (P->patch ? P->n_rg : go + 1); ++g) tiles.push_back(make_int4(l, g, x0, y0));
+          for (int g = go; g < (inner_g ? P->n_rg : go + 1); ++g) tiles.push_back(make_int4(l, g, x0, y0));
   P->n_tiles = (int)tiles.size();
   // Default: a persistent grid of at most 2048 workgroups (8 per CU).
   int grid = (tune && tune->grid > 0) ? tune->grid : (int)std::min<int64_t>(2048, ceil_div(P->n_tiles, 8) * 8);

@@ -588,8 +588,9 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
     H->levels = kHistSteps;
   }
   std::vector<int4> tiles;
-  // Patches with the r-groups innermost (the chunks of one site share cache lines).
-  const bool inner_g = H->patch.fn != nullptr;
+  // The r-groups innermost on patches and where a site's chunks are not whole 128-byte
+  // lines, which the groups then share.
+  const bool inner_g = H->patch.fn != nullptr || P->E % 8 != 0;
   for (int go = 0; go < (inner_g ? 1 : n_rg); ++go)
     for (int y0 = 0; y0 < L.L2; y0 += ty)
       for (int x0 = 0; x0 < L.L1; x0 += xstep)
