@@ -601,9 +601,15 @@ int kpm_bandwidth_probe(int32_t pattern, int64_t bytes_per_array, int32_t iters,
  * the moment (plans, networks, per-call workspaces; not the idle blocks that
  * kpm_release_workspace gives back), so a test can check that a failed call
  * released everything it allocated.
+ *
+ * kpm_debug_launches returns how many launches of one kind this process has made
+ * so far (launches captured into a graph count once), so that a test can check
+ * which path a call took: 0 patches, 1 patches of the conductivity chains, 2 row
+ * history sweeps, 3 single recursion steps; -1 for an unknown kind.
  */
 int32_t kpm_debug_inject_failure(int32_t nth, int32_t kind);
 int64_t kpm_debug_live_allocations(void);
+int64_t kpm_debug_launches(int32_t kind);
 
 #ifdef __cplusplus
 }

@@ -51,6 +51,7 @@ static std::atomic<int64_t> g_fault_countdown{0};
 static std::atomic<int32_t> g_fault_kind{0};
 static std::atomic<int32_t> g_fault_fired{0};
 static std::atomic<int64_t> g_live_allocs{0};
+static std::atomic<int64_t> g_launches[kLaunchKinds];
 
 bool fault_due() {
   int64_t c = g_fault_countdown.load(std::memory_order_relaxed);
@@ -71,6 +72,7 @@ hipError_t fault_error() {
 }
 
 void live_add(int64_t d) { g_live_allocs.fetch_add(d, std::memory_order_relaxed); }
+void count_launch(int kind) { g_launches[kind].fetch_add(1, std::memory_order_relaxed); }
 
 void set_error(const char* fmt, ...) {
   char buf[1024];
@@ -1557,6 +1559,7 @@ static hipError_t launch_step_t(kpm_plan* P, hipStream_t s, const StepLaunch& L)
 }
 
 hipError_t plan_launch_step(kpm_plan* P, hipStream_t s, const StepLaunch& L) {
+  count_launch(kLaunchStep);
   // Single steps need the single-step tile list (a sweep plan's tiles overlap).
   if (P->sweep > 1) return hipErrorInvalidValue;
   return P->prec == KPM_FP32 ? launch_step_t<float>(P, s, L) : launch_step_t<double>(P, s, L);
@@ -1793,6 +1796,10 @@ int32_t kpm_debug_inject_failure(int32_t nth, int32_t kind) {
   kpm::g_fault_kind.store(kind, std::memory_order_relaxed);
   kpm::g_fault_countdown.store(nth, std::memory_order_relaxed);
   return fired;
+}
+
+int64_t kpm_debug_launches(int32_t kind) {
+  return kind < 0 || kind >= kpm::kLaunchKinds ? -1 : kpm::g_launches[kind].load(std::memory_order_relaxed);
 }
 
 int64_t kpm_debug_live_allocations(void) { return kpm::g_live_allocs.load(std::memory_order_relaxed); }

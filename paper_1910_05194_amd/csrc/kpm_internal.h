@@ -36,6 +36,9 @@ inline hipError_t launch_status() { return after_call(hipGetLastError()); }
 // countdown, with a count of the buffers in use (kpm_debug_live_allocations) so
 // that the error-path tests can see every buffer released.
 void live_add(int64_t d);
+// Launches by kind (kpm_debug_launches), so that a test can see the path a call took.
+enum { kLaunchPatch, kLaunchPatchChain, kLaunchHistory, kLaunchStep, kLaunchKinds };
+void count_launch(int kind);
 hipError_t pool_malloc(void** p, size_t bytes);
 hipError_t pool_free(void* p);
 // hipMemGetInfo with the pool's idle blocks on the current device counted as free.

@@ -115,6 +115,7 @@ hipError_t patch_run(const kpm_plan* P, const PatchShape& S, hipStream_t s, cons
                      int n_tiles, const void* v, const void* w, int nlev, void* const* out, double* part,
                      int64_t part_stride) {
   if (nlev < 1 || nlev > S.ks) return hipErrorInvalidValue;
+  count_launch(kLaunchPatch);
   return P->prec == KPM_FP32
              ? launch_patch<float>(P, S, s, tiles, slot_of, n_tiles, v, w, nlev, out, part, part_stride)
              : launch_patch<double>(P, S, s, tiles, slot_of, n_tiles, v, w, nlev, out, part, part_stride);

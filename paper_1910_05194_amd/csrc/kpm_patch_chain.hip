@@ -217,6 +217,7 @@ static hipError_t launch(const kpm_plan* P, const ChainPlan& C, hipStream_t s, i
   void* args[] = {&a};
   void* fn = C.fn[mode][blk_lo != nullptr ? 1 : 0];
   if (fn == nullptr || nlev < 1 || nlev > S.ks) return hipErrorInvalidValue;
+  count_launch(kLaunchPatchChain);
   return after_call(hipLaunchKernel(fn, dim3((unsigned)(ceil_div(C.n_tiles, 8) * 8)), dim3(kPatchBlock), args, S.lds_bytes, s));
 }
 

@@ -514,6 +514,7 @@ void* sweep_kernel_fn(int prec, int kind, int ks, bool onsite, bool mask, bool p
 #include "kpm_plan.h"
 
 #include <algorithm>
+#include <cstdlib>
 #include <functional>
 
 namespace kpm {
@@ -542,6 +543,10 @@ double sweep_rows(const std::vector<kpm_lattice_t>& lats, int ks, int xstep, int
 int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
   *H = HistPlan();
   if (P->n_lat != 1) return KPM_E_UNSUPPORTED;
+  // KPM_HISTORY_STEPS: 1 keeps single steps, 2..4 row sweeps of at most that many.
+  int forced = 0;
+  if (const char* hs = std::getenv("KPM_HISTORY_STEPS"); hs && *hs) forced = std::max(1, std::min(std::atoi(hs), kHistSteps));
+  if (forced == 1) return KPM_E_UNSUPPORTED;
   int dev = 0, lds_max = 65536, n_cu = 256, v = 0;
   if (hipGetDevice(&dev) == hipSuccess) {
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0) lds_max = v;
@@ -575,7 +580,7 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
     conc = (int64_t)n_cu * std::max(1, std::min(kMaxStepBlock / block, (int)(lds_max / H->lds_bytes)));
     us = sweep_rows(P->lats, ks, xstep, n_rg, conc, &ty);
   }
-  if (patch_shape(P, true, max_levels, lds_max, n_cu, &H->patch) && H->patch.us_per_step < kPatchGain * us) {
+  if (forced == 0 && patch_shape(P, true, max_levels, lds_max, n_cu, &H->patch) && H->patch.us_per_step < kPatchGain * us) {
     block = kPatchBlock;
     ew = 1 << H->patch.lgw;
     n_rg = (int)ceil_div(P->E, ew);
@@ -585,7 +590,7 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
   } else {
     H->patch = PatchShape();
     if (block < 64) return KPM_E_UNSUPPORTED;
-    H->levels = kHistSteps;
+    H->levels = forced ? forced : kHistSteps;
   }
   std::vector<int4> tiles;
   // The r-groups innermost on patches and where a site's chunks are not whole 128-byte
@@ -650,6 +655,7 @@ hipError_t history_sweep(const kpm_plan* P, const HistPlan& H, hipStream_t s, co
                          void* const* out) {
   if (nlev < 1 || nlev > H.levels || H.fn == nullptr) return hipErrorInvalidValue;
   if (H.patch.fn) return patch_run(P, H.patch, s, H.tiles, nullptr, H.n_tiles, v, w, nlev, out, nullptr, 0);
+  count_launch(kLaunchHistory);
   return P->prec == KPM_FP32 ? history_launch<float>(P, H, s, v, w, nlev, out)
                              : history_launch<double>(P, H, s, v, w, nlev, out);
 }

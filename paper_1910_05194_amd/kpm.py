@@ -156,6 +156,7 @@ def _load():
         "kpm_release_workspace": (ctypes.c_int, [ctypes.POINTER(ctypes.c_int64)]),
         "kpm_debug_inject_failure": (ctypes.c_int32, [ctypes.c_int32, ctypes.c_int32]),
         "kpm_debug_live_allocations": (ctypes.c_int64, []),
+        "kpm_debug_launches": (ctypes.c_int64, [ctypes.c_int32]),
     }
     for name, (res, args) in sig.items():
         f = getattr(lib, name)
@@ -185,6 +186,12 @@ def debug_inject_failure(nth: int, kind: int = 0) -> int:
 def debug_live_allocations() -> int:
     """Device buffers the library holds right now (kpm_debug_live_allocations)."""
     return int(LIB.kpm_debug_live_allocations())
+
+
+def debug_launches(kind: int) -> int:
+    """Launches of one kind made so far (kpm_debug_launches): 0 patches, 1 chain patches, 2 row history
+    sweeps, 3 single steps."""
+    return int(LIB.kpm_debug_launches(int(kind)))
 
 
 def release_workspace() -> int:
