@@ -89,6 +89,7 @@ hipError_t chain_run(const kpm_plan* P, const ChainPlan& C, hipStream_t s, int m
 struct HistPlan {
   PatchShape patch;   // patch.fn: patches instead of row sweeps
   int levels = 0;     // steps per launch
+  int min_levels = 1; // fewer than these run as single steps
   int block = 0, Tx = 0, Ty = 0, Ew = 0, grid = 0, n_tiles = 0;
   size_t lds_bytes = 0;
   int4* tiles = nullptr;

@@ -540,6 +540,14 @@ double sweep_rows(const std::vector<kpm_lattice_t>& lats, int ks, int xstep, int
   return (4.0 + 1.25 * (double)best) / ks;
 }
 
+// The choice follows from launches of few levels.  A four-level sweep that forms one or
+// two still pays its halo columns and its skewed start: single steps took less on all of
+// 15 lattices (us, single steps -> one sweep; honeycomb 600 x 600, 13 vectors, FP64: one
+// level 175 -> 285, two 387 -> 438; 512 x 512, 4, FP32: 19 -> 35 and 44 -> 53).  Three
+// levels are about even (526 -> 521 with the 13 vectors, 360 -> 421 with 9, whose second
+// group holds one chunk of eight): the model decides.  Four won on all of them.
+constexpr int kHistMinLevels = 3;
+
 int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
   *H = HistPlan();
   if (P->n_lat != 1) return KPM_E_UNSUPPORTED;
@@ -578,7 +586,10 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
     xstep = H->Tx - 2 * (ks - 1);
     n_rg = (int)ceil_div(P->E, ew);
     conc = (int64_t)n_cu * std::max(1, std::min(kMaxStepBlock / block, (int)(lds_max / H->lds_bytes)));
-    us = sweep_rows(P->lats, ks, xstep, n_rg, conc, &ty);
+    const double launch = ks * sweep_rows(P->lats, ks, xstep, n_rg, conc, &ty);
+    const int levels = std::min(max_levels, ks);
+    if (forced || levels == ks || (levels >= kHistMinLevels && launch / levels < us)) us = launch / levels;
+    else block = 0;   // single steps
   }
   if (forced == 0 && patch_shape(P, true, max_levels, lds_max, n_cu, &H->patch) && H->patch.us_per_step < kPatchGain * us) {
     block = kPatchBlock;
@@ -591,6 +602,7 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
     H->patch = PatchShape();
     if (block < 64) return KPM_E_UNSUPPORTED;
     H->levels = forced ? forced : kHistSteps;
+    H->min_levels = forced ? 1 : kHistMinLevels;
   }
   std::vector<int4> tiles;
   // The r-groups innermost on patches and where a site's chunks are not whole 128-byte
@@ -661,17 +673,17 @@ hipError_t history_sweep(const kpm_plan* P, const HistPlan& H, hipStream_t s, co
 }
 
 // T_n x0 for n = n0 .. n1 - 1 (n0 >= 1) into the buffers at(n), from T_{n0-1} and
-// T_{n0-2}: history sweeps where the plan has them, else single steps.  A sweep
-// forms at most max_levels levels (the caller's buffers allow that many beside the
-// two it reads).
+// T_{n0-2}: history sweeps where the plan has them, else single steps, which also make
+// the last levels where too few are left for a sweep.  A sweep forms at most max_levels
+// levels (the caller's buffers allow that many beside the two it reads).
 hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, int n1, int max_levels,
                        const std::function<void*(int)>& at) {
   hipError_t e = hipSuccess;
   for (int n = n0; n < n1 && e == hipSuccess;) {
     const void* v = at(n - 1);
     const void* w = n >= 2 ? at(n - 2) : nullptr;
-    if (H && H->fn) {
-      const int nlev = std::min(std::min(H->levels, max_levels), n1 - n);
+    const int nlev = H && H->fn ? std::min(std::min(H->levels, max_levels), n1 - n) : 0;
+    if (nlev > 0 && nlev >= H->min_levels) {
       void* out[kPatchSteps];
       for (int l = 0; l < nlev; ++l) out[l] = at(n + l);
       e = history_sweep(P, *H, s, v, w, nlev, out);

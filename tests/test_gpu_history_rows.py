@@ -117,3 +117,16 @@ def test_gamma1_and_singleshot_on_rows(K, monkeypatch, kind):
             if ref is None:
                 ref = got
         assert np.array_equal(ref[0], got[0]) and np.array_equal(ref[1], got[1])
+
+
+@pytest.mark.parametrize("kind,prec", [("square", wl.FP64), ("honeycomb-on-vac-flux", wl.FP32)])
+def test_few_levels_run_as_single_steps(K, monkeypatch, kind, prec):
+    """Above the patches: M history vectors allow M - 2 levels per launch, and the last
+    launch of a run may have fewer left.  One or two levels are single steps."""
+    lat = _lattice(kind, 700, 600)
+    psi0 = np.ones((9, lat.n_orbitals), dtype=complex) / np.sqrt(lat.n_orbitals)
+    for M, rows, single in ((3, 0, 2), (4, 0, 3), (7, 1, 2), (38, 9, 2)):
+        got, n = _states(K, monkeypatch, None, lat, psi0, M, prec)
+        assert (n[PATCH], n[ROWS], n[STEP]) == (0, rows, single), (M, n)
+        one, _ = _states(K, monkeypatch, 1, lat, psi0, M, prec)
+        assert np.array_equal(got, one)
