@@ -419,9 +419,10 @@ int kpm_reconstruct_sigma_bastin(const double* gamma, int32_t M, const double* e
  * gamma_nm [M][M][2], gamma_n [M][2], omegas_ev [K], sigma [K][2] (re, im);
  * all host (on_device = 0) or all device pointers (the frequencies are copied
  * to the host either way).  Work: one M x 4 M x n_theta / 2 real product for all
- * frequencies and O(M n_theta) per frequency.  Allocates and frees a device
- * workspace (~32 M^2 bytes, up to 1 GB for blocks of the product and 16 K n_theta
- * for the frequencies); synchronises hip_stream.  Errors: KPM_E_INVALID (NULL, M outside
+ * frequencies (for each block of them where the product takes several blocks) and
+ * O(M n_theta) per frequency.  Allocates and frees a device workspace (~32 M^2
+ * bytes, up to 1 GB for blocks of the product and up to 1 GB for blocks of
+ * frequencies); synchronises hip_stream.  Errors: KPM_E_INVALID (NULL, M outside
  * [1, 16384], K outside [1, 65536], a frequency <= 0, e_min >= e_max,
  * eta <= 0, kT < 0, orbitals_per_nm2 <= 0, n_theta outside [0, 2^20]);
  * KPM_E_DEVICE.

@@ -952,10 +952,14 @@ extern "C" int kpm_reconstruct_sigma_optical(const double* gamma_nm, const doubl
   // Pairs of cells per block: V and U of a block take at most about 1 GB.
   const int64_t cap = ((int64_t)1 << 30) / (2 * (int64_t)sizeof(double) * sh.C) / kLT * kLT;
   const int nq_max = (int)std::min<int64_t>(ceil_div(sh.Qh, kLT) * kLT, std::max<int64_t>(kLT, cap));
+  // Frequencies per block: their sums per cell take at most about 1 GB.  V and U are
+  // formed again for each block of frequencies only where they come in several blocks.
+  const int k_max = (int)std::min<int64_t>(
+      K, std::max<int64_t>(kOptK, ((int64_t)1 << 30) / ((int64_t)sizeof(double2) * Q) / kOptK * kOptK));
   const size_t gn = (size_t)M * M * 2;
   Carve cv;
   const size_t o_b = cv.add(sizeof(double) * (size_t)sh.Mp * sh.C), o_d = cv.add(sizeof(double) * (size_t)sh.Mp * nq_max);
-  const size_t o_w = cv.add(2 * sizeof(double) * (size_t)nq_max * sh.C), o_p = cv.add(sizeof(double2) * (size_t)K * Q);
+  const size_t o_w = cv.add(2 * sizeof(double) * (size_t)nq_max * sh.C), o_p = cv.add(sizeof(double2) * (size_t)k_max * Q);
   const size_t o_x1 = cv.add(sizeof(double2) * (size_t)Q), o_occ = cv.add(sizeof(double) * (size_t)Q);
   const size_t o_cs = cv.add(kT_ev > 0.0 ? sizeof(double) * kFermiSub * (size_t)Q : 0);
   const size_t o_host = cv.add(on_device ? 0 : sizeof(double) * (gn + 2 * (size_t)M + 3 * (size_t)K));
@@ -984,25 +988,31 @@ extern "C" int kpm_reconstruct_sigma_optical(const double* gamma_nm, const doubl
     if (kT_ev > 0.0)
       hipLaunchKernelGGL(sub_cosine_kernel, dim3(qb, kFermiSub), dim3(256), 0, s, Q, at(o_cs));
     hipLaunchKernelGGL(occ_weights_kernel, dim3(qb), dim3(256), 0, s, Q, mut, kTt, at(o_cs), at(o_occ));
-    for (int q0 = 0; q0 < sh.Qh && e == hipSuccess; q0 += nq_max) {
-      ThetaRows rows = {Q, q0, std::min(nq_max, sh.Qh - q0), 0};
-      rows.nqp = (int)ceil_div(rows.nq, kLT) * kLT;
-      SeriesOut out;
-      out.W = at(o_w);
-      hipLaunchKernelGGL(theta_table_kernel, dim3((unsigned)ceil_div(rows.nqp, 256), sh.Mp / 16), dim3(256), 0, s, rows,
-                         M, at(o_d));
-      hipLaunchKernelGGL(optical_rank1_kernel, dim3(rows.nqp / 64), dim3(1024), 0, s, at(o_d), rows, M, dgn,
-                         (double2*)at(o_x1));
-      hipLaunchKernelGGL(series_gemm_kernel<false>, dim3(sh.C / kLT, rows.nqp / kLT), dim3(256), 0, s, at(o_d), at(o_b),
-                         rows, sh.Mp, sh.C, out);
-      hipLaunchKernelGGL(optical_para_kernel, dim3((unsigned)ceil_div(2 * (int64_t)rows.nq, 4), (unsigned)ceil_div(K, kOptK)),
-                         dim3(256), 0, s, at(o_w), rows, M, sh.C, dom, K, de_m, eta_ev / de_m, (double2*)at(o_p));
-      e = ::kpm::launch_status();
-    }
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(optical_final_kernel, dim3(K), dim3(256), 0, s, (double2*)at(o_x1), (double2*)at(o_p),
-                         at(o_occ), Q, dom, de_m, orbitals_per_nm2, dsig);
-      e = ::kpm::launch_status();
+    for (int k0 = 0; k0 < K && e == hipSuccess; k0 += k_max) {
+      const int kn = std::min(k_max, K - k0);
+      for (int q0 = 0; q0 < sh.Qh && e == hipSuccess; q0 += nq_max) {
+        ThetaRows rows = {Q, q0, std::min(nq_max, sh.Qh - q0), 0};
+        rows.nqp = (int)ceil_div(rows.nq, kLT) * kLT;
+        if (k0 == 0 || sh.Qh > nq_max) {
+          SeriesOut out;
+          out.W = at(o_w);
+          hipLaunchKernelGGL(theta_table_kernel, dim3((unsigned)ceil_div(rows.nqp, 256), sh.Mp / 16), dim3(256), 0, s,
+                             rows, M, at(o_d));
+          hipLaunchKernelGGL(optical_rank1_kernel, dim3(rows.nqp / 64), dim3(1024), 0, s, at(o_d), rows, M, dgn,
+                             (double2*)at(o_x1));
+          hipLaunchKernelGGL(series_gemm_kernel<false>, dim3(sh.C / kLT, rows.nqp / kLT), dim3(256), 0, s, at(o_d),
+                             at(o_b), rows, sh.Mp, sh.C, out);
+        }
+        hipLaunchKernelGGL(optical_para_kernel,
+                           dim3((unsigned)ceil_div(2 * (int64_t)rows.nq, 4), (unsigned)ceil_div(kn, kOptK)), dim3(256), 0,
+                           s, at(o_w), rows, M, sh.C, dom + k0, kn, de_m, eta_ev / de_m, (double2*)at(o_p));
+        e = ::kpm::launch_status();
+      }
+      if (e == hipSuccess) {
+        hipLaunchKernelGGL(optical_final_kernel, dim3(kn), dim3(256), 0, s, (double2*)at(o_x1), (double2*)at(o_p),
+                           at(o_occ), Q, dom + k0, de_m, orbitals_per_nm2, dsig + 2 * (size_t)k0);
+        e = ::kpm::launch_status();
+      }
     }
   }
   if (e == hipSuccess && !on_device) e = hipMemcpyAsync(sigma, dsig, sizeof(double) * 2 * K, hipMemcpyDeviceToHost, s);
