@@ -395,8 +395,8 @@ int kpm_reconstruct_sigma(const double* gamma, int32_t M, const double* energies
  * should then be narrower than a few kT).
  * gamma [M][M][2] (re, im) as kpm_moments_cond writes it, energies_ev [K]
  * Fermi energies, sigma [K]; all host (on_device = 0) or all device pointers.
- * Allocates a device workspace of ~16 M^2 + 4 n_theta M + 900 n_theta bytes and
- * frees it before returning; synchronises hip_stream.  Errors: KPM_E_INVALID (NULL, M outside [1, 16384], K < 1,
+ * Allocates a device workspace of ~16 M^2 + 5 n_theta M + 900 n_theta bytes and up to
+ * 256 MB for blocks of energies, and frees it before returning; synchronises hip_stream.  Errors: KPM_E_INVALID (NULL, M outside [1, 16384], K < 1,
  * e_min >= e_max, eta <= 0, kT < 0, orbitals_per_nm2 <= 0, n_theta outside
  * [0, 2^20]); KPM_E_DEVICE.
  */

@@ -706,6 +706,8 @@ extern "C" int kpm_reconstruct_sigma_bastin(const double* gamma, int32_t M, cons
   const SeriesShape sh(M, n_theta, 2);
   const int Q = sh.Q, nt = sh.C / kLT, ns = (int)ceil_div(Q, 256);
   const ThetaRows rows = {Q, 0, sh.Qh, (int)ceil_div(sh.Qh, kLT) * kLT};
+  // Energies per block: their partial sums take at most 256 MB.
+  const int k_max = std::min(K, std::max(1, (1 << 25) / ns));
   hipStream_t s = (hipStream_t)hip_stream;
   const double de_m = 0.5 * (e_max - e_min);
   const size_t gn = (size_t)M * M * 2;
@@ -713,7 +715,7 @@ extern "C" int kpm_reconstruct_sigma_bastin(const double* gamma, int32_t M, cons
   const size_t o_b = cv.add(sizeof(double) * (size_t)sh.Mp * sh.C), o_d = cv.add(sizeof(double) * (size_t)sh.Mp * rows.nqp);
   const size_t o_fine = cv.add(sizeof(double2) * 32 * (size_t)Q), o_coarse = cv.add(sizeof(double2) * (size_t)Q * nt);
   const size_t o_sc = cv.add(sizeof(double2) * 2 * (size_t)Q), o_part = cv.add(sizeof(double) * (size_t)Q * nt);
-  const size_t o_f = cv.add(sizeof(double) * (size_t)Q), o_ps = cv.add(sizeof(double) * (size_t)K * ns);
+  const size_t o_f = cv.add(sizeof(double) * (size_t)Q), o_ps = cv.add(sizeof(double) * (size_t)k_max * ns);
   const size_t o_cs = cv.add(kT_ev > 0.0 ? sizeof(double) * kFermiSub * (size_t)Q : 0);
   const size_t o_host = cv.add(on_device ? 0 : sizeof(double) * (gn + 2 * (size_t)K));
   char* ws = nullptr;
@@ -750,11 +752,14 @@ extern "C" int kpm_reconstruct_sigma_bastin(const double* gamma, int32_t M, cons
     hipLaunchKernelGGL(sum_tiles_kernel, dim3((unsigned)ceil_div(Q, 64)), dim3(64), 0, s, at(o_part), nt, Q, at(o_f));
     if (kT_ev > 0.0)
       hipLaunchKernelGGL(sub_cosine_kernel, dim3(qb, kFermiSub), dim3(256), 0, s, Q, at(o_cs));
-    hipLaunchKernelGGL(bastin_sigma_kernel, dim3(K, ns), dim3(256), 0, s, at(o_f), Q, den, e_min, e_max, kT_ev / de_m,
-                       at(o_cs), at(o_ps));
-    // pref = -2 pi i (N/Omega)/de-^2 is imaginary: Re(pref F) = -Im(pref) Im(F).
-    hipLaunchKernelGGL(bastin_final_kernel, dim3(K), dim3(256), 0, s, at(o_ps), ns,
-                       2.0 * M_PI * orbitals_per_nm2 / (de_m * de_m), dsig);
+    for (int k0 = 0; k0 < K; k0 += std::min(k_max, K - k0)) {
+      const int kn = std::min(k_max, K - k0);
+      hipLaunchKernelGGL(bastin_sigma_kernel, dim3(kn, ns), dim3(256), 0, s, at(o_f), Q, den + k0, e_min, e_max,
+                         kT_ev / de_m, at(o_cs), at(o_ps));
+      // pref = -2 pi i (N/Omega)/de-^2 is imaginary: Re(pref F) = -Im(pref) Im(F).
+      hipLaunchKernelGGL(bastin_final_kernel, dim3(kn), dim3(256), 0, s, at(o_ps), ns,
+                         2.0 * M_PI * orbitals_per_nm2 / (de_m * de_m), dsig + k0);
+    }
     e = ::kpm::launch_status();
   }
   if (e == hipSuccess && !on_device) {
@@ -988,7 +993,7 @@ extern "C" int kpm_reconstruct_sigma_optical(const double* gamma_nm, const doubl
     if (kT_ev > 0.0)
       hipLaunchKernelGGL(sub_cosine_kernel, dim3(qb, kFermiSub), dim3(256), 0, s, Q, at(o_cs));
     hipLaunchKernelGGL(occ_weights_kernel, dim3(qb), dim3(256), 0, s, Q, mut, kTt, at(o_cs), at(o_occ));
-    for (int k0 = 0; k0 < K && e == hipSuccess; k0 += k_max) {
+    for (int k0 = 0; k0 < K && e == hipSuccess; k0 += k_max) {   // (K <= 65536)
       const int kn = std::min(k_max, K - k0);
       for (int q0 = 0; q0 < sh.Qh && e == hipSuccess; q0 += nq_max) {
         ThetaRows rows = {Q, q0, std::min(nq_max, sh.Qh - q0), 0};

@@ -44,3 +44,19 @@ def test_optical_blocks_of_frequencies(K, M, Q, n, left):
         assert torch.equal(one[0], got[i]), i
     del fill
     torch.cuda.empty_cache()
+
+
+def test_bastin_blocks_of_energies(K):
+    """2^20 cells: 32 KB of partial sums per energy, 3.3 GB for 100000 on a card with 3 GB free."""
+    import torch
+    K.release_workspace()
+    torch.cuda.empty_cache()
+    fill = torch.empty(torch.cuda.mem_get_info()[0] - 3 * GIB, dtype=torch.uint8, device="cuda")
+    G = _gamma(2, "cuda")
+    E = torch.linspace(-6.9, 8.9, 100000, device="cuda", dtype=torch.float64)
+    args = dict(e_min=-7.0, e_max=9.0, eta=0.3, orbitals_per_nm2=30.0, n_theta=1 << 20)
+    got = K.reconstruct_sigma_bastin(G, E, **args)
+    idx = torch.tensor([0, 1, 8190, 8191, 8192, 8193, 65535, 99999], device="cuda")
+    assert torch.equal(K.reconstruct_sigma_bastin(G, E[idx], **args), got[idx])
+    del fill
+    torch.cuda.empty_cache()
