@@ -575,16 +575,16 @@ int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, Cha
   if (e != hipSuccess) {
     set_error("chain sweep setup: %s", hipGetErrorString(e));
     (void)hipGetLastError();
-    chain_plan_free(C);
+    chain_plan_free(C, false);
     return hip_status(e);
   }
   return KPM_OK;
 }
 
-void chain_plan_free(ChainPlan* C) {
-  (void)dev_free(C->tiles);
-  (void)dev_free(C->Z);
-  (void)dev_free(C->W);
+void chain_plan_free(ChainPlan* C, bool idle) {
+  (void)dev_free(C->tiles, idle);
+  (void)dev_free(C->Z, idle);
+  (void)dev_free(C->W, idle);
   C->tiles = nullptr;
   C->Z = C->W = nullptr;
 }

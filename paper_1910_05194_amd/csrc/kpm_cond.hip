@@ -270,11 +270,11 @@ static int cond_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double
     e = ::kpm::launch_status();
     if (e == hipSuccess && !on_dev)
       e = hipMemcpyAsync(gamma, gdev, (size_t)M * M * 2 * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) fail(e, "Gamma output");
-  } else {
-    (void)hipStreamSynchronize(s);
   }
+  const hipError_t se = hipStreamSynchronize(s);
+  P->idle = se == hipSuccess;
+  if (se != hipSuccess && st == KPM_OK) fail(se, "Gamma output");
   if (st == KPM_OK) {
     float ms_t = 0.f;
     if (hipEventRecord(ev[2], s) == hipSuccess && hipEventSynchronize(ev[2]) == hipSuccess &&
@@ -284,8 +284,8 @@ static int cond_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, double
   for (auto& x : ev)
     if (x) (void)hipEventDestroy(x);
   for (void* ptr : {Lb, Rblk, Llo, Rlo, (void*)acc, (void*)part, (void*)gdev})
-    if (ptr) (void)::kpm::dev_free(ptr);
-  chain_plan_free(&C);
+    if (ptr) (void)::kpm::dev_free(ptr, P->idle);
+  chain_plan_free(&C, P->idle);
   plan_free(P);
   delete P;
   return st;
@@ -492,17 +492,18 @@ static int gamma1_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, doub
     hipLaunchKernelGGL(gamma1_finish_kernel, dim3(M), dim3(256), 0, s, part, R, P->active, out);
     e = ::kpm::launch_status();
     if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(g1, gdev, (size_t)M * 2 * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-  } else {
-    (void)hipStreamSynchronize(s);
   }
+  // Waited for also after a failure: the buffers then serve other calls at once.
+  const hipError_t se = hipStreamSynchronize(s);
+  P->idle = se == hipSuccess;
+  if (e == hipSuccess) e = se;
   if (e != hipSuccess && st == KPM_OK) {
     set_error("kpm_moments_gamma1: %s", hipGetErrorString(e));
     st = (e == hipErrorOutOfMemory) ? KPM_E_NOMEM : KPM_E_DEVICE;
   }
   for (void* ptr : {U, hist, (void*)part, (void*)gdev})
-    if (ptr) (void)::kpm::dev_free(ptr);
-  hist_plan_free(&H);
+    if (ptr) (void)::kpm::dev_free(ptr, P->idle);
+  hist_plan_free(&H, P->idle);
   plan_free(P);
   delete P;
   return st;
@@ -759,17 +760,18 @@ static int singleshot_run(const kpm_lattice_t* lat, const kpm_cond_params_t* p, 
     hipLaunchKernelGGL(singleshot_finish_kernel, dim3(K), dim3(256), 0, s, part, 2.0 * M_PI * M_PI / (omega * R), out);
     e = ::kpm::launch_status();
     if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(sigma, dsig, sizeof(double) * K, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-  } else {
-    (void)hipStreamSynchronize(s);
   }
+  // Waited for also after a failure: the buffers then serve other calls at once.
+  const hipError_t se = hipStreamSynchronize(s);
+  P->idle = se == hipSuccess;
+  if (e == hipSuccess) e = se;
   if (e != hipSuccess && st == KPM_OK) {
     set_error("kpm_sigma_singleshot: %s", hipGetErrorString(e));
     st = (e == hipErrorOutOfMemory) ? KPM_E_NOMEM : KPM_E_DEVICE;
   }
   for (void* ptr : {V0, Sc, acc, hist, (void*)dcoef, (void*)part, (void*)dsig})
-    if (ptr) (void)::kpm::dev_free(ptr);
-  hist_plan_free(&H4);
+    if (ptr) (void)::kpm::dev_free(ptr, P->idle);
+  hist_plan_free(&H4, P->idle);
   plan_free(P);
   delete P;
   return st;

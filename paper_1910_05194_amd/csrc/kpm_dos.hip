@@ -1012,7 +1012,7 @@ void plan_free(kpm_plan* P) {
                   P->mu_dev, P->mean_dev};
   if (!P->use_arena)
     for (void* b : bufs)
-      if (b) (void)::kpm::dev_free(b);
+      if (b) (void)::kpm::dev_free(b, P->idle);
   if (P->graph_loop) (void)hipGraphExecDestroy(P->graph_loop);
   if (P->cap_stream) (void)hipStreamDestroy(P->cap_stream);
   for (auto& e : P->ev)
@@ -1691,6 +1691,7 @@ static int plan_run(kpm_plan* P, double* mu_pv, double* mu_mean, int32_t on_dev,
   KPM_CHECK_ARG(P != nullptr, "plan is NULL");
   hipStream_t s = (hipStream_t)stream;
   const bool timed = P->ev[0] != nullptr;
+  P->idle = false;
   if (timed) KPM_TRY_HIP(hipEventRecord(P->ev[0], s));
   KPM_TRY_HIP(plan_launch_prep(P, s));
   if (timed) KPM_TRY_HIP(hipEventRecord(P->ev[1], s));
@@ -1737,6 +1738,7 @@ static int plan_run(kpm_plan* P, double* mu_pv, double* mu_mean, int32_t on_dev,
                                hipMemcpyDeviceToHost, s));
   // Wait also after a failure: the copies write this frame's host memory.
   const hipError_t se = ::kpm::after_call(hipStreamSynchronize(s));
+  P->idle = se == hipSuccess;
   if (e == hipSuccess) e = se;
   if (e != hipSuccess) {
     set_error("reading the run's status flags: %s", hipGetErrorString(e));

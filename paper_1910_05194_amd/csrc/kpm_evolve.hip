@@ -327,16 +327,17 @@ static int wavepacket_run(const kpm_lattice_t* lat, int32_t n_k, const double* k
                        1.0 / std::sqrt(norm));
     e = ::kpm::launch_status();
     if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(psi, dpsi, sizeof(double) * 2 * (size_t)n, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-  } else {
-    (void)hipStreamSynchronize(s);
   }
+  // Waited for also after a failure: the buffers then serve other calls at once.
+  const hipError_t se = hipStreamSynchronize(s);
+  P->idle = se == hipSuccess;
+  if (e == hipSuccess) e = se;
   if (e != hipSuccess) {
     set_error("kpm_wavepacket_gaussian: %s", hipGetErrorString(e));
     st = ::kpm::hip_status(e);
   }
   for (void* ptr : {(void*)dk, (void*)dsp, (void*)part, (void*)dpsi})
-    if (ptr) (void)::kpm::dev_free(ptr);
+    if (ptr) (void)::kpm::dev_free(ptr, P->idle);
   plan_free(P);
   delete P;
   return st;
@@ -492,15 +493,17 @@ static int evolve_run(const kpm_lattice_t* lat, const kpm_evolve_params_t* p, do
   }
   if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(psi, dpsi, sizeof(double) * n_psi, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess && !on_dev) e = hipMemcpyAsync(observables, dobs, sizeof(double) * n_obs, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  else (void)hipStreamSynchronize(s);
+  // Waited for also after a failure: the buffers then serve other calls at once.
+  const hipError_t se = hipStreamSynchronize(s);
+  P->idle = se == hipSuccess;
+  if (e == hipSuccess) e = se;
   if (e != hipSuccess) {
     set_error("kpm_time_evolve: %s", hipGetErrorString(e));
     st = (e == hipErrorOutOfMemory) ? KPM_E_NOMEM : KPM_E_DEVICE;
   }
   for (void* ptr : {hist, (void*)dcoef, (void*)part, (void*)dpsi, (void*)dobs})
-    if (ptr) (void)::kpm::dev_free(ptr);
-  hist_plan_free(&H4);
+    if (ptr) (void)::kpm::dev_free(ptr, P->idle);
+  hist_plan_free(&H4, P->idle);
   plan_free(P);
   delete P;
   return st;

@@ -40,11 +40,11 @@ void live_add(int64_t d);
 enum { kLaunchPatch, kLaunchPatchChain, kLaunchHistory, kLaunchStep, kLaunchKinds };
 void count_launch(int kind);
 hipError_t pool_malloc(void** p, size_t bytes);
-hipError_t pool_free(void* p);
+hipError_t pool_free(void* p, bool idle);
 // hipMemGetInfo with the pool's idle blocks on the current device counted as free.
 hipError_t mem_available(size_t* free_bytes, size_t* total_bytes);
-// pooled = false: plain hipMalloc, for calls that a program may make while it
-// captures (reusing an idle block may synchronise the device).
+// pooled = false: plain hipMalloc, for buffers that calls without a wait at their end
+// keep using (the networks').
 template <typename T>
 inline hipError_t dev_malloc(T** p, size_t bytes, bool pooled = true) {
   if (fault_due()) {
@@ -57,10 +57,12 @@ inline hipError_t dev_malloc(T** p, size_t bytes, bool pooled = true) {
   else *p = nullptr;
   return e;
 }
-inline hipError_t dev_free(void* p) {
+// idle: the caller has waited for all work on the block (and the wait succeeded), so it
+// may serve another call at once.  Otherwise it goes back to the device, which waits.
+inline hipError_t dev_free(void* p, bool idle = false) {
   if (!p) return hipSuccess;
   live_add(-1);
-  return pool_free(p);
+  return pool_free(p, idle);
 }
 
 #define KPM_TRY_HIP_STATUS_(expr, text)                                                    \

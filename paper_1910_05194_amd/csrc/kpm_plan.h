@@ -69,7 +69,7 @@ struct ChainPlan {
 // fits the LDS or a lattice row is too long for 32-bit offsets (the caller
 // then runs single steps).
 int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, ChainPlan* C);
-void chain_plan_free(ChainPlan* C);
+void chain_plan_free(ChainPlan* C, bool idle);
 // n_levels recursion levels from level 0 in v0 (level 1 = H~ v0, then 2 H~ v - w),
 // with one Gamma block row per level: mode 0 stores levels 1..n_levels into rows
 // 1..n_levels; mode 1 stores the velocity vel_scale [r^vdir, H] of levels
@@ -99,7 +99,7 @@ struct HistPlan {
 double sweep_rows(const std::vector<kpm_lattice_t>& lats, int ks, int xstep, int n_rg, int64_t conc, int* ty);
 // For launches of at most max_levels steps.  KPM_E_UNSUPPORTED: the caller runs single steps.
 int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H);
-void hist_plan_free(HistPlan* H);
+void hist_plan_free(HistPlan* H, bool idle);
 hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, int n1, int max_levels,
                        const std::function<void*(int)>& at);
 // The model (site arrays, Peierls table, active-orbital count) and the start vectors (into X).
@@ -156,6 +156,7 @@ struct kpm_plan {
   int sweep = 1;               // Chebyshev steps per launch (variant - 1 for the sweep kernels, else 1)
   size_t lds_bytes = 0;
   bool patch = false;          // the steps run on patches (sweep of them per launch)
+  bool idle = false;           // a wait has covered all work on the plan's buffers
   kpm::PatchShape patch_sh;
   int64_t r_base = 0;          // global index of the plan's first random vector
   hipStream_t cap_stream = nullptr;

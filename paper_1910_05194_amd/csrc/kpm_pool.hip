@@ -16,9 +16,10 @@
 // - an allocation that fails gives every idle block back and tries once more;
 // - kpm_release_workspace() gives them back on request;
 // - a block serves a request only if it is at most an eighth larger (or 64 KB).
-// A block is handed out again only after its device has been synchronised since
-// its release (hipFree would have waited at the release), so it may be used on
-// any stream, and a call that failed with work in flight may simply release.
+// Only blocks whose caller has waited for its work become idle, so that they may be
+// used on any stream at once; those of a call that failed before or in its wait go
+// through hipFree, which waits.  The pool itself never synchronises: a device-wide
+// wait fails, and invalidates the capture, while any thread captures a stream.
 // One mutex covers the bookkeeping; blocks in use by different threads are
 // distinct.
 
@@ -40,7 +41,6 @@ struct Block {
   void* p;
   size_t cap;
   int dev;
-  uint64_t freed;   // release count when it became idle
 };
 
 // The idle blocks of one device.
@@ -54,8 +54,6 @@ struct Pool {
   std::mutex mu;
   std::unordered_map<void*, Block> used;
   std::list<Block> idle;                        // oldest first
-  uint64_t releases = 0;
-  std::unordered_map<int, uint64_t> synced;     // per device: release count before its last synchronisation
   std::unordered_map<int, Idle> idle_of;
 };
 
@@ -111,13 +109,6 @@ hipError_t pool_malloc(void** out, size_t bytes) {
           (best == P.idle.end() || it->cap < best->cap))
         best = it;
     if (best != P.idle.end()) {
-      uint64_t& synced = P.synced[dev];
-      if (best->freed > synced) {
-        const uint64_t now = P.releases;
-        e = hipDeviceSynchronize();
-        if (e != hipSuccess) return e;
-        synced = now;
-      }
       P.used.emplace(best->p, *best);
       *out = best->p;
       drop(P, best);
@@ -131,7 +122,7 @@ hipError_t pool_malloc(void** out, size_t bytes) {
     }
     if (e != hipSuccess) return e;
     try {
-      P.used.emplace(p, Block{p, need, dev, 0});
+      P.used.emplace(p, Block{p, need, dev});
     } catch (...) {
       (void)hipFree(p);
       return hipErrorOutOfMemory;
@@ -143,7 +134,7 @@ hipError_t pool_malloc(void** out, size_t bytes) {
   }
 }
 
-hipError_t pool_free(void* p) {
+hipError_t pool_free(void* p, bool idle) {
   try {
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
@@ -152,7 +143,7 @@ hipError_t pool_free(void* p) {
     Block b = it->second;
     P.used.erase(it);
     int cur = 0;
-    bool keep = hipGetDevice(&cur) == hipSuccess && cur == b.dev;   // (another device's limits are not at hand)
+    bool keep = idle && hipGetDevice(&cur) == hipSuccess && cur == b.dev;   // (another device's limits are not at hand)
     if (keep) {
       Idle& d = P.idle_of[b.dev];
       d.unseen += b.cap;
@@ -166,7 +157,6 @@ hipError_t pool_free(void* p) {
       trim(P, b.dev, keep ? d.bound - b.cap : d.bound, kMaxIdle - 1);
     }
     if (keep) {
-      b.freed = ++P.releases;
       try {
         Idle& d = P.idle_of[b.dev];
         P.idle.push_back(b);

@@ -90,14 +90,15 @@ extern "C" int kpm_bandwidth_probe(int32_t pattern, int64_t bytes_per_array, int
   float* red = nullptr;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int st = KPM_OK;
+  hipError_t e = hipSuccess;
   auto cleanup = [&]() {
-    if (a) (void)::kpm::dev_free(a);
-    if (b) (void)::kpm::dev_free(b);
-    if (red) (void)::kpm::dev_free(red);
+    if (a) (void)::kpm::dev_free(a, e == hipSuccess);
+    if (b) (void)::kpm::dev_free(b, e == hipSuccess);
+    if (red) (void)::kpm::dev_free(red, e == hipSuccess);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
   };
-  hipError_t e = ::kpm::dev_malloc(&a, n * 16);
+  e = ::kpm::dev_malloc(&a, n * 16);
   if (e == hipSuccess) e = ::kpm::dev_malloc(&b, n * 16);
   if (e == hipSuccess) e = ::kpm::dev_malloc(&red, (size_t)grid * block * sizeof(float));
   if (e == hipSuccess) e = hipEventCreate(&e0);

@@ -199,7 +199,7 @@ extern "C" int kpm_reconstruct_sigma(const double* gamma, int32_t M, const doubl
     e = hipMemcpyAsync(sigma, dsig, sizeof(double) * K, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
   }
-  if (tmp) (void)::kpm::dev_free(tmp);
+  if (tmp) (void)::kpm::dev_free(tmp, e == hipSuccess);   // (host output: waited for)
   if (e != hipSuccess) {
     set_error("kpm_reconstruct_sigma: %s", hipGetErrorString(e));
     return ::kpm::hip_status(e);
@@ -246,7 +246,7 @@ static int reconstruct(const char* name, int which, const double* mu, int32_t M,
     if (e == hipSuccess && green) e = hipMemcpyAsync(green, dg, sizeof(double) * 2 * K, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
   }
-  if (tmp) (void)::kpm::dev_free(tmp);
+  if (tmp) (void)::kpm::dev_free(tmp, e == hipSuccess);   // (host output: waited for)
   if (e != hipSuccess) {
     set_error("%s: %s", name, hipGetErrorString(e));
     return ::kpm::hip_status(e);
@@ -279,7 +279,7 @@ extern "C" int kpm_kernel_factors(int32_t kernel, int32_t M, double lambda, int3
     e = hipMemcpyAsync(g, dg, sizeof(double) * (size_t)count, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
   }
-  if (!on_device) (void)::kpm::dev_free(dg);
+  if (!on_device) (void)::kpm::dev_free(dg, e == hipSuccess);
   if (e != hipSuccess) {
     kpm::set_error("kpm_kernel_factors: %s", hipGetErrorString(e));
     return ::kpm::hip_status(e);
@@ -766,7 +766,7 @@ extern "C" int kpm_reconstruct_sigma_bastin(const double* gamma, int32_t M, cons
     e = hipMemcpyAsync(sigma, dsig, sizeof(double) * K, hipMemcpyDeviceToHost, s);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)::kpm::dev_free(ws);
+  (void)::kpm::dev_free(ws, e == hipSuccess);
   if (e != hipSuccess) {
     set_error("kpm_reconstruct_sigma_bastin: %s", hipGetErrorString(e));
     return ::kpm::hip_status(e);
@@ -1022,7 +1022,7 @@ extern "C" int kpm_reconstruct_sigma_optical(const double* gamma_nm, const doubl
   }
   if (e == hipSuccess && !on_device) e = hipMemcpyAsync(sigma, dsig, sizeof(double) * 2 * K, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)::kpm::dev_free(ws);
+  (void)::kpm::dev_free(ws, e == hipSuccess);
   if (e != hipSuccess) {
     set_error("kpm_reconstruct_sigma_optical: %s", hipGetErrorString(e));
     return ::kpm::hip_status(e);

@@ -626,14 +626,14 @@ int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H) {
   if (e != hipSuccess) {
     set_error("history sweep setup: %s", hipGetErrorString(e));
     (void)hipGetLastError();
-    hist_plan_free(H);
+    hist_plan_free(H, false);
     return hip_status(e);
   }
   return KPM_OK;
 }
 
-void hist_plan_free(HistPlan* H) {
-  (void)dev_free(H->tiles);
+void hist_plan_free(HistPlan* H, bool idle) {
+  (void)dev_free(H->tiles, idle);
   *H = HistPlan();
 }
 
