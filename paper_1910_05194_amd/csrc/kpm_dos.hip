@@ -655,26 +655,45 @@ __global__ void __launch_bounds__(kMaxStepBlock) step_kernel_ring(StepArgs<T> A)
 // ---------------------------------------------------------------------------
 struct ModelLat {
   int64_t site_off, n_sites, vec_off;
+  int64_t start_wg;   // workgroups of the lattices before this one: start vectors,
+  int model_wg;       // model build
   double W, p, de_p, de_m;
   uint64_t key_anderson, key_vacancy;
   int n_spin;
 };
 
-// grid = (workgroups striding over the sites, lattices).  Active orbitals are
-// counted per workgroup: one atomic per wave of 64 sites met at one address
-// (6.3 ms for 33.5M sites, 0.10 ms for 0.5M; now 0.06 ms and 4 us).
+// The lattice that workgroup wg of a launch over a batch belongs to: the last one whose
+// first workgroup is not beyond it.
+template <typename F>
+__device__ inline int lattice_of(int n_lat, int64_t wg, F first) {
+  int lo = 0, hi = n_lat - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first(mid) <= wg) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// A workgroup takes span consecutive sites of one lattice (span: all sites over about
+// 2048 workgroups, so that a batch launches no more than one lattice of its size and a
+// workgroup each for the smallest).  Active orbitals are counted per workgroup: one
+// atomic per wave of 64 sites met at one address (6.3 ms for 33.5M sites, 0.10 ms for
+// 0.5M; now 0.06 ms and 4 us).
 template <typename T>
-__global__ void __launch_bounds__(256) model_kernel(const ModelLat* ml, T* onsite, uint8_t* mask,
+__global__ void __launch_bounds__(256) model_kernel(const ModelLat* ml, int n_lat, int span, T* onsite, uint8_t* mask,
                                                     unsigned long long* active) {
   __shared__ unsigned int count[4];
-  const int lat = blockIdx.y;
+  const int lat = lattice_of(n_lat, blockIdx.x, [&](int l) { return (int64_t)ml[l].model_wg; });
   const ModelLat m = ml[lat];
+  const int64_t first = (int64_t)((int)blockIdx.x - m.model_wg) * span;
   if (!onsite && !mask) {   // a clean batch: nothing to store, every site is active
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(active + lat, (unsigned long long)m.n_sites * m.n_spin);
+    if (first == 0 && threadIdx.x == 0) atomicAdd(active + lat, (unsigned long long)m.n_sites * m.n_spin);
     return;
   }
   unsigned int n = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m.n_sites; i += (int64_t)gridDim.x * 256) {
+  const int64_t last = min(first + span, m.n_sites);
+  for (int64_t i = first + threadIdx.x; i < last; i += 256) {
     bool alive = true;
     double V = 0.0;
     if (m.W != 0.0) V = m.W * (sm_uniform(m.key_anderson, (uint64_t)i) - 0.5);
@@ -722,24 +741,24 @@ __global__ void phase_kernel(const PhaseLat* pl, T* phase) {
 }
 
 // Start vectors: random phases exp(2 pi i u) (FP64, rounded once), zero on
-// vacant sites and on padded vectors.  grid = (256 packs per workgroup, lattices);
-// a workgroup's first pack is split into orbital and chunk once, its threads add
-// 32-bit quotients.
+// vacant sites and on padded vectors.  256 packs of one lattice per workgroup; its
+// first pack is split into orbital and chunk once, its threads add 32-bit quotients.
 template <typename T>
-__global__ void __launch_bounds__(256) start_phase_kernel(T* x, const ModelLat* ml, int R, int Rp, const uint64_t* keys,
-                                                          const uint8_t* mask) {
+__global__ void __launch_bounds__(256) start_phase_kernel(T* x, const ModelLat* ml, int n_lat, int64_t wg0, int R, int Rp,
+                                                          const uint64_t* keys, const uint8_t* mask) {
   using P = Pack<T>;
   constexpr int NC = P::NC;
-  const ModelLat m = ml[blockIdx.y];
+  const int64_t wg = wg0 + blockIdx.x;
+  const int lat = lattice_of(n_lat, wg, [&](int l) { return ml[l].start_wg; });
+  const ModelLat m = ml[lat];
   const uint32_t E = Rp / NC;
-  const int64_t first = (int64_t)blockIdx.x * 256;
-  if (first >= m.n_sites * m.n_spin * E) return;
+  const int64_t first = (wg - m.start_wg) * 256;
   const int64_t o0 = first / E;
   const uint32_t t = (uint32_t)(first - o0 * E) + threadIdx.x;
   const int64_t o = o0 + t / E;
   const int c = (int)(t % E);
   if (o >= m.n_sites * m.n_spin) return;
-  const uint64_t* key = keys + (size_t)blockIdx.y * Rp;
+  const uint64_t* key = keys + (size_t)lat * Rp;
   const bool alive = mask ? (mask[m.site_off + (m.n_spin == 2 ? o >> 1 : o)] != 0) : true;
   P p;
 #pragma unroll
@@ -758,8 +777,7 @@ __global__ void __launch_bounds__(256) start_phase_kernel(T* x, const ModelLat* 
 
 template <typename T>
 __global__ void fill_zero_kernel(T* x, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) x[i] = (T)0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) x[i] = (T)0;
 }
 
 template <typename T>
@@ -1406,12 +1424,17 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
     for (int r = 0; r < P->Rp; ++r) keys[(size_t)l * P->Rp + r] = sm_key(kPurposePhase, p->vector_seed, l, r);
   std::vector<ModelLat> ml(n_lat);
   std::vector<PhaseLat> pl(n_lat);
+  P->model_span = (int)ceil_div(ceil_div(P->n_sites, 2048), 256) * 256;
   const Geometry g = honeycomb_geometry();
   for (int l = 0; l < n_lat; ++l) {
     const kpm_lattice_t& L = lat[l];
     ml[l].site_off = P->site_off[l];
     ml[l].n_sites = (int64_t)L.L1 * L.L2 * P->n_sub;
     ml[l].vec_off = P->vec_off[l];
+    ml[l].start_wg = P->start_wgs;
+    ml[l].model_wg = P->model_wgs;
+    P->start_wgs += ceil_div(ml[l].n_sites * P->n_spin * P->E, 256);
+    P->model_wgs += (int)ceil_div(ml[l].n_sites, P->model_span);
     ml[l].W = L.anderson_w;
     ml[l].p = L.vacancy_p;
     ml[l].de_p = 0.5 * (L.e_max + L.e_min);
@@ -1487,35 +1510,32 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
 template <typename T>
 static hipError_t launch_prep(kpm_plan* P, hipStream_t s, int what) {
   T* X = (T*)P->X;
-  int64_t max_sites = 0, max_l1 = 0;
-  for (const kpm_lattice_t& L : P->lats) {
-    max_sites = std::max(max_sites, (int64_t)L.L1 * L.L2 * P->n_sub);
-    max_l1 = std::max<int64_t>(max_l1, L.L1);
-  }
-  // Lattices run along the grid's second dimension.
-  for (int l0 = 0; l0 < P->n_lat; l0 += 32768) {
-    const unsigned nl = (unsigned)std::min(32768, P->n_lat - l0);
-    const ModelLat* ml = P->mlat + l0;
-    if (what & kPrepModel) {
-      hipLaunchKernelGGL(zero_u64, dim3(ceil_div(nl, 256)), dim3(256), 0, s, P->active + l0, (int)nl);
-      hipLaunchKernelGGL(model_kernel<T>, dim3((unsigned)std::min<int64_t>(ceil_div(max_sites, 256), 2048), nl),
-                         dim3(256), 0, s, ml, (T*)P->onsite, P->mask, P->active + l0);
-      if (P->has_phase)
-        hipLaunchKernelGGL(phase_kernel<T>, dim3(ceil_div(max_l1 * 3, 256), nl), dim3(256), 0, s, P->plat + l0,
-                           (T*)P->phase);
+  const ModelLat* ml = P->mlat;
+  if (what & kPrepModel) {
+    hipLaunchKernelGGL(zero_u64, dim3(ceil_div(P->n_lat, 256)), dim3(256), 0, s, P->active, P->n_lat);
+    hipLaunchKernelGGL(model_kernel<T>, dim3(P->model_wgs), dim3(256), 0, s, ml, P->n_lat, P->model_span,
+                       (T*)P->onsite, P->mask, P->active);
+    if (P->has_phase) {
+      int64_t max_l1 = 0;
+      for (const kpm_lattice_t& L : P->lats) max_l1 = std::max<int64_t>(max_l1, L.L1);
+      for (int l0 = 0; l0 < P->n_lat; l0 += 32768)   // lattices along the grid's second dimension
+        hipLaunchKernelGGL(phase_kernel<T>, dim3(ceil_div(max_l1 * 3, 256), std::min(32768, P->n_lat - l0)), dim3(256), 0,
+                           s, P->plat + l0, (T*)P->phase);
     }
-    if (what & kPrepStart) {
-      if (P->p.start == KPM_START_RANDOM_PHASE) {
-        hipLaunchKernelGGL(start_phase_kernel<T>, dim3(ceil_div(max_sites * P->n_spin * P->E, 256), nl), dim3(256), 0,
-                           s, X, ml, P->R, P->Rp, P->keys + (size_t)l0 * P->Rp, P->mask);
-      } else {
-        if (l0 == 0) {
-          const int64_t n = P->n_orb * P->Rp * 2;
-          hipLaunchKernelGGL(fill_zero_kernel<T>, dim3(ceil_div(n, 256)), dim3(256), 0, s, X, n);
-        }
-        hipLaunchKernelGGL(start_sites_kernel<T>, dim3(ceil_div(P->R, 256), nl), dim3(256), 0, s, X, ml, P->d_sites,
-                           P->R, P->Rp);
-      }
+  }
+  if (what & kPrepStart) {
+    if (P->p.start == KPM_START_RANDOM_PHASE) {
+      // (A launch has fewer than 2^32 threads.)
+      for (int64_t w0 = 0; w0 < P->start_wgs; w0 += 1 << 23)
+        hipLaunchKernelGGL(start_phase_kernel<T>, dim3((unsigned)std::min<int64_t>(1 << 23, P->start_wgs - w0)), dim3(256),
+                           0, s, X, ml, P->n_lat, w0, P->R, P->Rp, P->keys, P->mask);
+    } else {
+      const int64_t n = P->n_orb * P->Rp * 2;
+      hipLaunchKernelGGL(fill_zero_kernel<T>, dim3((unsigned)std::min<int64_t>(ceil_div(n, 256), 1 << 20)), dim3(256), 0,
+                         s, X, n);
+      for (int l0 = 0; l0 < P->n_lat; l0 += 32768)
+        hipLaunchKernelGGL(start_sites_kernel<T>, dim3(ceil_div(P->R, 256), std::min(32768, P->n_lat - l0)), dim3(256), 0, s,
+                           X, ml + l0, P->d_sites, P->R, P->Rp);
     }
   }
   return ::kpm::launch_status();

@@ -155,6 +155,8 @@ struct kpm_plan {
   int variant = 2;             // 1 = direct-load step kernel, 2 = LDS row ring, 3..6 = 2..5 steps per sweep
   int sweep = 1;               // Chebyshev steps per launch (variant - 1 for the sweep kernels, else 1)
   size_t lds_bytes = 0;
+  int64_t start_wgs = 0;       // workgroups of the start-vector launch over all lattices
+  int model_wgs = 0, model_span = 256;   // and of the model build, each of model_span sites
   bool patch = false;          // the steps run on patches (sweep of them per launch)
   bool idle = false;           // a wait has covered all work on the plan's buffers
   kpm::PatchShape patch_sh;
