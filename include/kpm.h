@@ -104,7 +104,8 @@ typedef struct kpm_dos_params_t {
 
 /* Optional launch shape of the Chebyshev step kernel (0 = library choice / autotune cache).  With block,
  * rows, grid, kernel and chunks all 0, lattices too small to fill the chip with rows run on square patches
- * held in LDS, 2..8 steps per launch; kpm_plan_info then gives the patch's cells as rows and tile_cells_x. */
+ * held in LDS, 2..8 steps per launch; kpm_plan_info then gives the patch's cells as rows and tile_cells_x,
+ * and the shape it gives (kernel, block, rows, grid, tile_chunks), passed here, selects the same patches. */
 typedef struct kpm_tune_t {
   int32_t block;           /* threads per workgroup (64..512, multiple of 64); 0 = 512 for the sweep kernels
                               (less where their row rings would not fit in LDS), 256 otherwise */
@@ -199,16 +200,19 @@ int kpm_moments_dos_noalloc(const kpm_lattice_t* lat, int32_t n_lat, const kpm_d
 /*
  * Launch-shape autotuner (the analogue of the paper's user-tuned TILE size,
  * Sec. 3(b) and Table 1).  Runs the recursion for probe_steps steps with each
- * candidate (kernel variant 1..6 x block x rows x grid x chunks) on the given
- * workload, timed with hipEvents on hip_stream, re-times the three fastest on
+ * candidate (kernel variant 1..6 x block x rows x grid x chunks, and the shape that
+ * the library chooses by itself: patches, or rows of fewer than 2048 tiles) on the
+ * given workload, timed with hipEvents on hip_stream, re-times the three fastest on
  * 4 probe_steps steps (median of three rounds), and returns the one with the
  * shortest time per step in *best (and its algorithmic GB/s in *best_gbs, may
  * be NULL; the sweep variants move fewer bytes per step, so GB/s does not rank
  * variants).  If cache_path is non-NULL the
  * result is appended to that text file; kpm_plan_create reads the file named
  * by the environment variable KPM_TUNE_CACHE whenever it is called without a
- * launch shape (tune NULL or all of block, rows, grid, kernel zero).  Allocates
- * one full-size plan at a time.
+ * launch shape (tune NULL or all of block, rows, grid, kernel zero).  Where the
+ * library's own shape won, *best holds what that is for this workload, and the
+ * file's line stands for the library's choice for any lattice it applies to.
+ * Allocates one full-size plan at a time.
  */
 int kpm_autotune(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t* p, int32_t probe_steps,
                  const char* cache_path, kpm_tune_t* best, double* best_gbs, void* hip_stream);

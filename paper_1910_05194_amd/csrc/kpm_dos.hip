@@ -1038,12 +1038,13 @@ void plan_free(kpm_plan* P) {
 }
 
 int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t* p,
-                       const kpm_tune_t* tune, kpm_plan** out, int (*arena_get)(char**), size_t arena_cap) {
+                       const kpm_tune_t* tune, kpm_plan** out, int (*arena_get)(char**), size_t arena_cap,
+                       bool use_cache) {
   KPM_CHECK_ARG(out != nullptr, "plan output pointer is NULL");
   *out = nullptr;
   // No launch shape given: use the autotune cache (KPM_TUNE_CACHE) if it has one.
   kpm_tune_t cached;
-  if (lat != nullptr && n_lat >= 1 && p != nullptr &&
+  if (use_cache && lat != nullptr && n_lat >= 1 && p != nullptr &&
       (!tune || (tune->block == 0 && tune->rows == 0 && tune->grid == 0 && tune->kernel == 0 && tune->chunks == 0))) {
     std::memset(&cached, 0, sizeof(cached));
     cached.use_graph = tune ? tune->use_graph : 1;
@@ -1263,9 +1264,22 @@ int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t*
   // They need four vectors as the sweeps do; in a caller's arena the single-step kernels
   // keep their two, so that no workload outgrows it.
   const bool shape_given = tune && (tune->block > 0 || tune->rows > 0 || tune->grid > 0 || tune->kernel > 0 || tune->chunks > 0);
-  if (!shape_given && room && (!P->use_arena || P->variant >= 3) && patch_shape(P, false, patch_steps(P->kind), lds_max, n_cu, &P->patch_sh) &&
-      P->patch_sh.us_per_step < kPatchGain * us_per_step) {
+  // A shape that names the patches as kpm_plan_info and the tuner report them means them too.
+  const bool patch_given = tune && tune->block == kPatchBlock && tune->rows > 0 && tune->grid > 0 && tune->kernel > 0 && tune->chunks > 0;
+  bool patch = (!shape_given || patch_given) && room && (!P->use_arena || P->variant >= 3) &&
+               patch_shape(P, false, patch_steps(P->kind), lds_max, n_cu, &P->patch_sh);
+  if (patch && shape_given) {
+    const int w = 1 << P->patch_sh.lgw;
+    int64_t n = 0;
+    for (int l = 0; l < n_lat; ++l)
+      n += ceil_div(P->E, w) * ceil_div(lat[l].L1, P->patch_sh.px) * ceil_div(lat[l].L2, P->patch_sh.py);
+    patch = tune->rows == P->patch_sh.py && tune->chunks == w && tune->grid == ceil_div(n, 8) * 8;
+  } else if (patch) {
+    patch = P->patch_sh.us_per_step < kPatchGain * us_per_step;
+  }
+  if (patch) {
     P->patch = true;
+    if (shape_given) P->variant = want;
     P->sweep = P->patch_sh.ks;
     P->block = kPatchBlock;
     P->Ew = 1 << P->patch_sh.lgw;

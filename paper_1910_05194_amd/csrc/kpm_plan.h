@@ -108,9 +108,10 @@ hipError_t plan_launch_prep(kpm_plan* P, hipStream_t s, int what = kPrepModel | 
 int plan_set_vector_base(kpm_plan* P, int64_t r0);
 // arena_get != nullptr: after the arguments are validated, arena_get supplies a device arena of
 // arena_cap bytes; every device buffer is carved from it instead of hipMalloc, and no stream, event
-// or graph is created (the allocation-free entry point).
+// or graph is created (the allocation-free entry point).  use_cache = false: the tuner's
+// own plans, which do not look into its cache.
 int plan_create(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t* p, const kpm_tune_t* tune,
-                kpm_plan** out, int (*arena_get)(char**) = nullptr, size_t arena_cap = 0);
+                kpm_plan** out, int (*arena_get)(char**) = nullptr, size_t arena_cap = 0, bool use_cache = true);
 void plan_free(kpm_plan* P);
 bool tune_cache_lookup(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_params_t* p, kpm_tune_t* t);
 double cell_area_nm2(int kind);

@@ -4,10 +4,12 @@
 // tune it per machine (Sec. 3(b); Sec. 5, Table 1).  Here the analogous
 // choices are the kernel variant (one step or 2..5 steps per sweep),
 // workgroup size, rows per tile, the site chunks a tile covers and the
-// persistent grid; kpm_autotune measures each candidate on the real workload
-// (a short recursion of probe_steps steps, timed with hipEvents on the
-// caller's stream) and records the fastest in a plain-text cache keyed by
-// (lattice kind, precision, padded vectors per orbital, floor(log2 orbitals)).
+// persistent grid; kpm_autotune measures each candidate, and the shape that the
+// library chooses by itself, on the real workload (a short recursion of
+// probe_steps steps, timed with hipEvents on the caller's stream) and records
+// the fastest in a plain-text cache keyed by (lattice kind, precision, padded
+// vectors per orbital, floor(log2 orbitals)).  A line that ends in "auto" stands
+// for the library's choice, whatever that is for the lattice at hand.
 // kpm_plan_create consults the cache named by the KPM_TUNE_CACHE environment
 // variable when the caller passes no launch shape.
 
@@ -64,6 +66,8 @@ bool tune_cache_lookup(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_pa
     int kind, prec, rp, lg, kern, block, rows, grid, chunks;
     double gbs;
     if (!(is >> kind >> prec >> rp >> lg >> kern >> block >> rows >> grid >> chunks >> gbs)) continue;
+    std::string word;
+    if (is >> word && word == "auto") kern = block = rows = grid = chunks = 0;
     if (kind == k.kind && prec == k.prec && rp == k.rp && lg == k.log2n) {
       t->kernel = kern;
       t->block = block;
@@ -76,7 +80,7 @@ bool tune_cache_lookup(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_pa
   return found;
 }
 
-static int tune_cache_store(const char* path, const TuneKey& k, const kpm_tune_t& t, double gbs) {
+static int tune_cache_store(const char* path, const TuneKey& k, const kpm_tune_t& t, double gbs, bool own) {
   if (!path || !*path) return KPM_OK;
   std::lock_guard<std::mutex> lock(g_cache_mu);
   std::ofstream f(path, std::ios::app);
@@ -85,7 +89,7 @@ static int tune_cache_store(const char* path, const TuneKey& k, const kpm_tune_t
     return KPM_E_INVALID;
   }
   f << k.kind << ' ' << k.prec << ' ' << k.rp << ' ' << k.log2n << ' ' << t.kernel << ' ' << t.block << ' ' << t.rows
-    << ' ' << t.grid << ' ' << t.chunks << ' ' << gbs << '\n';
+    << ' ' << t.grid << ' ' << t.chunks << ' ' << gbs << (own ? " auto" : "") << '\n';
   return KPM_OK;
 }
 
@@ -124,8 +128,12 @@ static int autotune(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_param
   // on a 1024-workgroup grid so that each workgroup still takes several tiles.  Duplicates of an
   // already screened shape and shapes that fell back to fewer steps are
   // skipped.
+  // The library's own shape comes first: patches, which no other candidate names
+  // (64 x 64 honeycomb, 4 vectors, FP64: 1.5 us a step against 4.1 for the best
+  // rows), or its rows, where they are few enough tiles (under 2048; beyond, the
+  // rows below come within some per cent of it).
   struct Cand { int kernel, block, rows, grid, chunks; };
-  std::vector<Cand> cands;
+  std::vector<Cand> cands = {{0, 0, 0, 0, 0}};
   for (int kv : {1, 2})
     for (int b : {256, 512})
       for (int r : {32, 128})
@@ -138,7 +146,9 @@ static int autotune(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_param
           if (r < 256 || c == 0) cands.push_back({kv, b, r, r >= 256 ? 1024 : 2048, c});
     }
   std::vector<std::pair<double, kpm_tune_t>> screened;
-  std::vector<std::array<int, 5>> seen;   // (variant, block, rows, grid, chunks in use)
+  kpm_tune_t own_shape;   // what the library's own shape is for this workload
+  std::memset(&own_shape, 0, sizeof(own_shape));
+  std::vector<std::array<int, 6>> seen;   // (variant, block, rows, grid, chunks in use, patches)
   for (const Cand& cd : cands) {
     kpm_tune_t t;
     std::memset(&t, 0, sizeof(t));
@@ -149,11 +159,23 @@ static int autotune(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_param
     t.chunks = cd.chunks;
     t.use_graph = 1;
     kpm_plan* P = nullptr;
-    int st = plan_create(lat, n_lat, &q, &t, &P);
+    int st = plan_create(lat, n_lat, &q, &t, &P, nullptr, 0, false);
     if (st != KPM_OK) return st;
-    const std::array<int, 5> shape = {P->variant, P->block, P->Ty, P->grid, P->Ew};
-    // Fell back (LDS, lattice kind) or same shape as an earlier candidate: skip.
-    if (P->variant != cd.kernel || std::find(seen.begin(), seen.end(), shape) != seen.end()) {
+    const std::array<int, 6> shape = {P->variant, P->block, P->Ty, P->grid, P->Ew, P->patch ? 1 : 0};
+    bool skip;
+    if (cd.kernel == 0) {
+      own_shape.kernel = P->variant;
+      own_shape.block = P->block;
+      own_shape.rows = P->Ty;
+      own_shape.grid = P->grid;
+      own_shape.chunks = P->patch ? P->Ew : 0;
+      own_shape.use_graph = 1;
+      skip = !P->patch && P->n_tiles >= 2048;
+    } else {
+      // Fell back (LDS, lattice kind) or same shape as an earlier candidate.
+      skip = P->variant != cd.kernel || std::find(seen.begin(), seen.end(), shape) != seen.end();
+    }
+    if (skip) {
       plan_free(P);
       delete P;
       continue;
@@ -181,7 +203,7 @@ static int autotune(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_param
   for (int rep = 0; rep < 3; ++rep)
     for (int i = 0; i < n_fin; ++i) {
       kpm_plan* P = nullptr;
-      int st = plan_create(lat, n_lat, &q2, &screened[i].second, &P);
+      int st = plan_create(lat, n_lat, &q2, &screened[i].second, &P, nullptr, 0, false);
       if (st != KPM_OK) return st;
       double r = 0.0, g = 0.0;
       st = kpm_plan_run(P, nullptr, nullptr, 1, stream);
@@ -202,9 +224,10 @@ static int autotune(const kpm_lattice_t* lat, int32_t n_lat, const kpm_dos_param
       bi = i;
     }
   }
-  *best = screened[bi].second;
+  const bool own = screened[bi].second.kernel == 0;
+  *best = own ? own_shape : screened[bi].second;
   if (best_gbs) *best_gbs = bgbs;
-  return tune_cache_store(cache_path, make_key(lat, n_lat, p), *best, bgbs);
+  return tune_cache_store(cache_path, make_key(lat, n_lat, p), *best, bgbs, own);
 }
 
 }  // namespace kpm
