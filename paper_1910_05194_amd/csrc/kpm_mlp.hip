@@ -25,7 +25,7 @@ typedef float f32x16m __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8m __attribute__((ext_vector_type(8)));
 
 constexpr int kGemmThreads = 256;  // four waves
-constexpr int kChunk = 64;         // contraction indices per LDS stage
+constexpr int kChunk = 64;         // contraction indices per LDS stage (32 in the products of large batches)
 constexpr int kLossBlocks = 256;   // partial sums of the stand-alone loss
 constexpr double kBeta1 = 0.9, kBeta2 = 0.999;
 
@@ -74,13 +74,16 @@ __device__ inline void adam_update(float g, const AdamArgs& a, float* p, float* 
 }
 
 // LDS of one product: two stages of the operand panels, k-major.
+// (80 floats a row are two workgroups per CU at CH = 64; 81 would be one.)
+template <int CH>
 struct GemmLds {
-  float a[2][kChunk * 80], b[2][kChunk * 80];
+  static constexpr int kRow = CH == kChunk ? 80 : 81;
+  float a[2][CH * kRow], b[2][CH * kRow];
 };
 
-// Staging of a panel op(X)[k0 .. k0 + 63][x0 .. x0 + W - 1] by 256 threads,
-// W / 16 groups of four values each: KC = the operand's rows are contiguous in k
-// (16 threads take the 64 k of one index), else contiguous in the index (W / 4
+// Staging of a panel op(X)[k0 .. k0 + CH - 1][x0 .. x0 + W - 1] by 256 threads,
+// CH W / 1024 groups of four values each: KC = the operand's rows are contiguous in k
+// (CH / 4 threads take the k of one index), else contiguous in the index (W / 4
 // threads take the indices of one k).  Values outside are zero.
 // LDS pitch: an MFMA operand read takes 16 indices of four k rows, the transposed
 // (KC) store 16 k quads of four indices.  W + 16 puts the four rows of a read in
@@ -90,14 +93,14 @@ struct GemmLds {
 // range, which reads as zero, so that no branch (whose merge would wait for every
 // load in flight) stands around a load.  NORM: the values are standardised by
 // feature on their way to LDS; the features run along k (KC) or the index.
-template <bool KC, bool VEC, int W, bool NORM>
+template <bool KC, bool VEC, int W, bool NORM, int CH>
 struct Panel {
-  static constexpr int G = W / 16;   // 64 W / (4 * 256)
+  static constexpr int G = CH * W / 1024, kQuads = CH / 4;
   static constexpr int kPitch = W + 16 + (KC ? 1 : 0);
   float x[G][4], sh[NORM ? G : 1][4], sc[NORM ? G : 1][4];
-  __device__ static int idx(int g) { return KC ? (int)(threadIdx.x / 16) + 16 * g : 4 * (int)(threadIdx.x % (W / 4)); }
+  __device__ static int idx(int g) { return KC ? (int)(threadIdx.x / kQuads) + (256 / kQuads) * g : 4 * (int)(threadIdx.x % (W / 4)); }
   __device__ static int kk(int g) {
-    return KC ? 4 * (int)(threadIdx.x % 16) : (int)(threadIdx.x / (W / 4)) + (1024 / W) * g;
+    return KC ? 4 * (int)(threadIdx.x % kQuads) : (int)(threadIdx.x / (W / 4)) + (1024 / W) * g;
   }
   __device__ static void load4(__amdgpu_buffer_rsrc_t r, uint32_t off, float (&v)[4]) {
     const float4 u = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
@@ -164,24 +167,25 @@ struct Panel {
 // product; these take 9..21 us, 30 % of it MFMA (the rest: LDS and L2 latency at
 // one wave per SIMD), and the weight updates 29..36 us (half of it Adam's 24 bytes
 // per parameter).  24 training steps: 28.1 -> 3.8 ms.
-template <bool TA, bool TB, int NW, int EPI, bool VEC, bool NORM>
-__device__ inline void gemm_tile(const Gemm& g, int tile, GemmLds& lds) {
+template <bool TA, bool TB, int NW, int EPI, bool VEC, bool NORM, int CH = kChunk>
+__device__ inline void gemm_tile(const Gemm& g, int tile, GemmLds<CH>& lds) {
   constexpr int W = 32 * NW;
   const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
   const int wave = threadIdx.x >> 6;
   const int wi = (wave & 1) * 16 * NW, wj = (wave >> 1) * 16 * NW;
   const int m0 = (tile % g.tm) * W, n0 = (tile / g.tm) * W;
-  const int chunks = (g.K + kChunk - 1) / kChunk;
-  using PA = Panel<!TA, VEC, W, NORM>;
-  using PB = Panel<TB, VEC, W, false>;
+  const int chunks = (g.K + CH - 1) / CH;
+  using PA = Panel<!TA, VEC, W, NORM, CH>;
+  using PB = Panel<TB, VEC, W, false, CH>;
+  static_assert(PA::kPitch <= GemmLds<CH>::kRow && PB::kPitch <= GemmLds<CH>::kRow, "panels fit their stages");
   PA pa[2];
   PB pb[2];
   auto load = [&](int c, PA& a, PB& b) {
-    a.load(g, g.A, g.lda, m0, g.M, c * kChunk, g.K);
-    b.load(g, g.B, g.ldb, n0, g.N, c * kChunk, g.K);
+    a.load(g, g.A, g.lda, m0, g.M, c * CH, g.K);
+    b.load(g, g.B, g.ldb, n0, g.N, c * CH, g.K);
   };
   auto store = [&](int c, PA& a, const PB& b, int st) {
-    a.standardise(m0, g.M, c * kChunk, g.K);
+    a.standardise(m0, g.M, c * CH, g.K);
     a.store(lds.a[st]);
     b.store(lds.b[st]);
   };
@@ -194,10 +198,10 @@ __device__ inline void gemm_tile(const Gemm& g, int tile, GemmLds& lds) {
   const bool colsum = (EPI == EPI_GRAD || EPI == EPI_ADAM) && m0 == 0 && (int)threadIdx.x < W;
   float col = 0.f;
   auto product = [&](int st) {
-    // Operands of eight steps of four indices at a time, the next batch on its way
+    // Operands of CH / 8 steps of four indices at a time, the next batch on its way
     // from LDS while one is multiplied (with one wave per SIMD a read before each
     // MFMA costs its whole latency).
-    constexpr int H = 8;
+    constexpr int H = CH / 8;
     float a[2][H][NW], b[2][H][NW];
     auto read = [&](int h, int set) {
 #pragma unroll
@@ -210,8 +214,8 @@ __device__ inline void gemm_tile(const Gemm& g, int tile, GemmLds& lds) {
     };
     read(0, 0);
 #pragma unroll
-    for (int h = 0; h < kChunk / (4 * H); ++h) {
-      if (h + 1 < kChunk / (4 * H)) read(h + 1, (h + 1) & 1);
+    for (int h = 0; h < CH / (4 * H); ++h) {
+      if (h + 1 < CH / (4 * H)) read(h + 1, (h + 1) & 1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int s = 0; s < H; ++s)
@@ -223,7 +227,7 @@ __device__ inline void gemm_tile(const Gemm& g, int tile, GemmLds& lds) {
     }
     if (colsum) {
 #pragma unroll 16
-      for (int k = 0; k < kChunk; ++k) col += lds.b[st][k * PB::kPitch + threadIdx.x];
+      for (int k = 0; k < CH; ++k) col += lds.b[st][k * PB::kPitch + threadIdx.x];
     }
   };
   load(0, pa[0], pb[0]);
@@ -339,11 +343,11 @@ __device__ inline void gemm_tile(const Gemm& g, int tile, GemmLds& lds) {
 // weights, read it through one L2.
 __device__ inline int xcd_tile() { return (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)); }
 
-template <bool TA, bool TB, int NW, int EPI, bool VEC, bool NORM>
+template <bool TA, bool TB, int NW, int EPI, bool VEC, bool NORM, int CH = kChunk>
 __global__ void __launch_bounds__(kGemmThreads) mlp_gemm(Gemm g) {
-  __shared__ GemmLds lds;
+  __shared__ GemmLds<CH> lds;
   const int tile = xcd_tile();
-  if (tile < g.tm * g.tn) gemm_tile<TA, TB, NW, EPI, VEC, NORM>(g, tile, lds);
+  if (tile < g.tm * g.tn) gemm_tile<TA, TB, NW, EPI, VEC, NORM, CH>(g, tile, lds);
 }
 
 __device__ inline void sum_partials(const double* partial, int n, double* out, double* red) {
@@ -363,7 +367,7 @@ __device__ inline void sum_partials(const double* partial, int n, double* out, d
 // the layer above it, whose weights the first no longer needs.
 template <int EPIW, bool VEC>
 __global__ void __launch_bounds__(kGemmThreads) mlp_back_pair(Gemm act, Gemm wgt) {
-  __shared__ GemmLds lds;
+  __shared__ GemmLds<kChunk> lds;
   const int tile = xcd_tile(), na = act.tm * act.tn;
   if (tile < na) gemm_tile<false, true, 1, EPI_GELU_BACK, VEC, false>(act, tile, lds);
   else if (tile - na < wgt.tm * wgt.tn) gemm_tile<true, false, 2, EPIW, VEC, false>(wgt, tile - na, lds);
@@ -374,7 +378,7 @@ __global__ void __launch_bounds__(kGemmThreads) mlp_back_pair(Gemm act, Gemm wgt
 template <int EPIW, bool VEC, bool NORM>
 __global__ void __launch_bounds__(kGemmThreads) mlp_weight_pair(Gemm g1, Gemm g2, const double* partial, int n_partial,
                                                                 double* loss) {
-  __shared__ GemmLds lds;
+  __shared__ GemmLds<kChunk> lds;
   const int tile = xcd_tile(), n1 = g1.tm * g1.tn, n2 = g2.tm * g2.tn;
   if (tile < n1) gemm_tile<true, false, 2, EPIW, VEC, false>(g1, tile, lds);
   else if (tile - n1 < n2) gemm_tile<true, false, 2, EPIW, VEC, NORM>(g2, tile - n1, lds);
@@ -716,15 +720,27 @@ static void set_tiles(Gemm& g, int nw) {
 static bool vector_loads(const Gemm& g) { return aligned16(g.A, g.lda) && aligned16(g.B, g.ldb); }
 
 // C = epilogue(A B), A [M][K], B [K][N].
-template <int EPI>
-static void gemm_forward(Gemm& g, hipStream_t s) {
-  set_tiles(g, 1);
-  auto fn = vector_loads(g) ? mlp_gemm<false, false, 1, EPI, true, false> : mlp_gemm<false, false, 1, EPI, false, false>;
+template <int EPI, int NW, int CH>
+static void gemm_forward_tiles(Gemm& g, hipStream_t s) {
+  set_tiles(g, NW);
+  auto fn = vector_loads(g) ? mlp_gemm<false, false, NW, EPI, true, false, CH> : mlp_gemm<false, false, NW, EPI, false, false, CH>;
   if constexpr (EPI == EPI_GELU) {
     if (g.x_shift)
-      fn = vector_loads(g) ? mlp_gemm<false, false, 1, EPI, true, true> : mlp_gemm<false, false, 1, EPI, false, true>;
+      fn = vector_loads(g) ? mlp_gemm<false, false, NW, EPI, true, true, CH> : mlp_gemm<false, false, NW, EPI, false, true, CH>;
   }
   hipLaunchKernelGGL(fn, xcd_grid((int64_t)g.tm * g.tn), dim3(kGemmThreads), 0, s, g);
+}
+// Large batches: from 384 tiles of 64 x 64 on (one and a half per CU) the product is no
+// longer bound by its chain but by how often the panels are read, and by the loads in
+// flight where they are scalar: 64 x 64 tiles with stages of 32 indices (41 KB, three
+// workgroups per CU).  FP32 inference, 32 x 32 tiles -> these: 256-1024-1792, batch 1024
+// 111 -> 99 us, 65536 6084 -> 3778; 255-1023-1791 (scalar loads), 65536 10655 -> 5442;
+// at 128 and 224 tiles a layer 67 -> 78, at 256 and 192 39 -> 43.  The sums run in the
+// same order: same bits.
+template <int EPI>
+static void gemm_forward(Gemm& g, hipStream_t s) {
+  if (ceil_div(g.M, 64) * ceil_div(g.N, 64) >= 384) gemm_forward_tiles<EPI, 2, 32>(g, s);
+  else gemm_forward_tiles<EPI, 1, kChunk>(g, s);
 }
 
 static Gemm layer_gemm(kpm_mlp* N, const float* A, int ni, int layer, int no, int B) {
