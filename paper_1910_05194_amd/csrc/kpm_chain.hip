@@ -550,9 +550,14 @@ int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, Cha
         for (int g = 0; g < (int)ceil_div(P->E, 1 << S.lgw); ++g) tiles.push_back(make_int4(0, g, x0, y0));
   } else {
     C->patch = PatchShape();
-    for (int g = 0; g < n_rg; ++g)
+    // The r-groups innermost where a site's chunks are not whole 128-byte lines, which the
+    // groups then share (honeycomb 600 x 600, 13 vectors, FP64, 20 orders: 6.30 ms of
+    // chains with the groups apart, 4.60 with them together).
+    const bool inner_g = P->E % 8 != 0;
+    for (int go = 0; go < (inner_g ? 1 : n_rg); ++go)
       for (int y0 = 0; y0 < L.L2; y0 += best_ty)
-        for (int x0 = 0; x0 < L.L1; x0 += xstep) tiles.push_back(make_int4(0, g, x0, y0));
+        for (int x0 = 0; x0 < L.L1; x0 += xstep)
+          for (int g = go; g < (inner_g ? n_rg : go + 1); ++g) tiles.push_back(make_int4(0, g, x0, y0));
   }
   C->ks = ks;
   C->block = block;
