@@ -536,7 +536,11 @@ int chain_plan_create(const kpm_plan* P, int ks, int rows, int64_t blk_rows, Cha
   // now 48), and a honeycomb 128 x 128 one (2, FP64) 32 tiles of 12 (16 us, now 8.8).
   int best_ty = rows;
   double us_per_step = 0.0;
-  if (rows <= 0) us_per_step = sweep_rows(P->lats, ks, xstep, n_rg, conc, &best_ty);
+  // In FP64 two workgroups on a CU take twice as long as one (honeycomb 236 x 926, 2
+  // vectors: 372 tiles of 5 rows 25.7 us a launch, 206 of 9 rows 22; in FP32 even), so
+  // that the rounds count one per CU.
+  if (rows <= 0)
+    us_per_step = sweep_rows(P->lats, ks, xstep, n_rg, P->prec == KPM_FP64 ? std::min<int64_t>(conc, n_cu) : conc, &best_ty);
   std::vector<int4> tiles;
   // Small spinless lattices run on patches, where the model sees a clear gain: 128 x 128,
   // 2 vectors, FP64: 1.61 -> 1.01 ms for all moments of order 128.  A spinful site's 2 x 2
