@@ -495,8 +495,10 @@ typedef struct kpm_evolve_stats_t {
   int32_t time_steps;         /* num_points - 1 */
   double loop_ms;             /* the time-step loop with its observables (hipEvents on the call's stream;
                                  excludes workspace allocation, model build and the copies in and out) */
-  double bytes;               /* algorithmic HBM bytes of the loop: per recursion step v_n, v_(n-1),
-                                 v_(n+1) and the per-site arrays; per flush the history vectors read
+  double bytes;               /* algorithmic HBM bytes of the loop: per launch of the recursion two
+                                 vectors and the per-site arrays read and one vector per step that it
+                                 makes (1; up to 4 by rows, 8 on patches) written; per flush the history
+                                 vectors read
                                  and psi(t + dt) written (and read after the first flush) */
 } kpm_evolve_stats_t;
 int kpm_evolve_last_stats(kpm_evolve_stats_t* stats);

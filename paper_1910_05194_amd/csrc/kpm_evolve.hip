@@ -372,18 +372,16 @@ static hipError_t evolve_loop(kpm_plan* P, const kpm_evolve_params_t* p, const C
   if (e == hipSuccess) e = hipEventCreate(&ev1);
   if (e == hipSuccess) e = hipEventRecord(ev0, s);
   if (e == hipSuccess) e = observe(0);
-  // Algorithmic bytes, counted in single steps also where a launch makes several: a
-  // recursion step reads v_n (neighbours from cache) and v_(n-1), writes v_(n+1),
-  // reads the per-site arrays; a flush reads its history vectors and writes
-  // psi(t + dt) (reading it too after the first).
-  const double site_b = (double)n_sites * ((P->has_onsite ? (double)sizeof(T) : 0.0) + (P->has_mask ? 1.0 : 0.0));
+  // Algorithmic bytes: a launch of the recursion reads two vectors (neighbours from
+  // cache) and the per-site arrays and writes one vector per step it makes; a flush
+  // reads its history vectors and writes psi(t + dt) (reading it too after the first).
   const int n_flush = (M + B - 1) / B;
-  const double step_b = (double)(M - 1) * (3.0 * (double)vec_b + site_b) + ((double)M + 2.0 * n_flush - 1.0) * (double)vec_b;
+  double bytes = ((double)M + 2.0 * n_flush - 1.0) * (double)vec_b * (p->num_points - 1);
   for (int k = 1; k < p->num_points && e == hipSuccess; ++k) {
     const std::function<void*(int)> at = hvec;
     for (int n0 = 0; n0 < M && e == hipSuccess; n0 += B) {
       const int n1 = std::min(M, n0 + B);
-      e = history_run(P, &H4, s, std::max(1, n0), n1, B - 2, at);
+      e = history_run(P, &H4, s, std::max(1, n0), n1, B - 2, at, &bytes);
       if (e == hipSuccess) e = flush(n0, n1 - n0, n0 == 0 ? 1 : 0);
     }
     std::swap(psi, nxt);
@@ -398,7 +396,7 @@ static hipError_t evolve_loop(kpm_plan* P, const kpm_evolve_params_t* p, const C
   g_evo_stats.history = B;
   g_evo_stats.time_steps = p->num_points - 1;
   g_evo_stats.loop_ms = ms;
-  g_evo_stats.bytes = step_b * (p->num_points - 1);
+  g_evo_stats.bytes = bytes;
   // The final state ends in X (copied out by the caller).
   if (e == hipSuccess && psi != P->X) e = hipMemcpyAsync(P->X, psi, vec_b, hipMemcpyDeviceToDevice, s);
   return e;

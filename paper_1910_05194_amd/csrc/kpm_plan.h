@@ -101,7 +101,7 @@ double sweep_rows(const std::vector<kpm_lattice_t>& lats, int ks, int xstep, int
 int hist_plan_create(const kpm_plan* P, int max_levels, HistPlan* H);
 void hist_plan_free(HistPlan* H, bool idle);
 hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, int n1, int max_levels,
-                       const std::function<void*(int)>& at);
+                       const std::function<void*(int)>& at, double* bytes = nullptr);
 // The model (site arrays, Peierls table, active-orbital count) and the start vectors (into X).
 enum { kPrepModel = 1, kPrepStart = 2 };
 hipError_t plan_launch_prep(kpm_plan* P, hipStream_t s, int what = kPrepModel | kPrepStart);

@@ -675,15 +675,21 @@ hipError_t history_sweep(const kpm_plan* P, const HistPlan& H, hipStream_t s, co
 // T_n x0 for n = n0 .. n1 - 1 (n0 >= 1) into the buffers at(n), from T_{n0-1} and
 // T_{n0-2}: history sweeps where the plan has them, else single steps, which also make
 // the last levels where too few are left for a sweep.  A sweep forms at most max_levels
-// levels (the caller's buffers allow that many beside the two it reads).
+// levels (the caller's buffers allow that many beside the two it reads).  *bytes is
+// increased by the algorithmic bytes: per launch two vectors and the site arrays in and
+// a vector per level out.
 hipError_t history_run(kpm_plan* P, const HistPlan* H, hipStream_t s, int n0, int n1, int max_levels,
-                       const std::function<void*(int)>& at) {
+                       const std::function<void*(int)>& at, double* bytes) {
+  const double vec_b = (double)P->n_orb * P->Rp * 2 * P->tsize;
+  const double site_b = (double)P->n_sites * ((P->has_onsite ? (double)P->tsize : 0.0) + (P->has_mask ? 1.0 : 0.0));
   hipError_t e = hipSuccess;
   for (int n = n0; n < n1 && e == hipSuccess;) {
     const void* v = at(n - 1);
     const void* w = n >= 2 ? at(n - 2) : nullptr;
     const int nlev = H && H->fn ? std::min(std::min(H->levels, max_levels), n1 - n) : 0;
-    if (nlev > 0 && nlev >= H->min_levels) {
+    const bool sweep = nlev > 0 && nlev >= H->min_levels;
+    if (bytes) *bytes += (2.0 + (sweep ? nlev : 1)) * vec_b + site_b;
+    if (sweep) {
       void* out[kPatchSteps];
       for (int l = 0; l < nlev; ++l) out[l] = at(n + l);
       e = history_sweep(P, *H, s, v, w, nlev, out);

@@ -130,3 +130,19 @@ def test_few_levels_run_as_single_steps(K, monkeypatch, kind, prec):
         assert (n[PATCH], n[ROWS], n[STEP]) == (0, rows, single), (M, n)
         one, _ = _states(K, monkeypatch, 1, lat, psi0, M, prec)
         assert np.array_equal(got, one)
+
+
+@pytest.mark.parametrize("prec", [wl.FP32, wl.FP64], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("kind", ["square", "honeycomb-on-vac"])
+def test_stats_count_the_launches_made(K, monkeypatch, kind, prec):
+    """kpm_evolve_stats_t.bytes: two vectors in and one per level out for each launch.
+    M = 38 with 32 history vectors: runs of 31 and 6 steps."""
+    lat = _lattice(kind, 40, 30)
+    psi0 = np.ones((2, lat.n_orbitals), dtype=complex) / np.sqrt(lat.n_orbitals)
+    size = 4 if prec == wl.FP32 else 8
+    vec = lat.n_orbitals * 2 * 2 * size
+    site = 0 if kind == "square" else lat.n_orbitals * (size + 1)
+    for steps, launches in ((1, [1] * 37), (4, [4] * 7 + [3, 4, 2]), (2, [2] * 15 + [1, 2, 2, 2])):
+        _states(K, monkeypatch, steps, lat, psi0, 38, prec)
+        want = sum((2 + n) * vec + site for n in launches) + (38 + 2 * 2 - 1) * vec
+        assert K.evolve_last_stats()["bytes"] == pytest.approx(want, rel=1e-12), steps
