@@ -383,16 +383,17 @@ __global__ void __launch_bounds__(256) gamma_columns_kernel(const double* __rest
   __shared__ double2 tr[32][33];
   const int n0 = blockIdx.y * 32, m0 = blockIdx.x * 32;
   const int x = threadIdx.x % 32, y = threadIdx.x / 32;
-  const double2* G = reinterpret_cast<const double2*>(gamma);
+  // (The caller's array is aligned to its doubles only.)
+  auto G = [&](int64_t i) { return make_double2(gamma[2 * i], gamma[2 * i + 1]); };
   for (int j = y; j < 32; j += 8) {
     const int m = m0 + j, n = n0 + x;
-    tr[j][x] = (m < M && n < M) ? G[(int64_t)m * M + n] : make_double2(0.0, 0.0);
+    tr[j][x] = (m < M && n < M) ? G((int64_t)m * M + n) : make_double2(0.0, 0.0);
   }
   __syncthreads();
   for (int j = y; j < 32; j += 8) {
     const int n = n0 + j, m = m0 + x;
     if (n >= Mp || NCOL * m >= C) continue;
-    const double2 a = (n < M && m < M) ? G[(int64_t)n * M + m] : make_double2(0.0, 0.0);
+    const double2 a = (n < M && m < M) ? G((int64_t)n * M + m) : make_double2(0.0, 0.0);
     const double2 b = tr[x][j];
     double* dst = B + (int64_t)n * C + NCOL * m;
     if constexpr (NCOL == 2) {

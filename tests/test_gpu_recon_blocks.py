@@ -60,3 +60,20 @@ def test_bastin_blocks_of_energies(K):
     assert torch.equal(K.reconstruct_sigma_bastin(G, E[idx], **args), got[idx])
     del fill
     torch.cuda.empty_cache()
+
+
+def test_gamma_aligned_to_its_doubles(K):
+    """A device Gamma whose first element lies 8 bytes past a 16-byte boundary."""
+    import torch
+    M = 70
+    G = _gamma(M, "cuda")
+    buf = torch.zeros(2 * M * M + 1, device="cuda", dtype=torch.float64)
+    buf[1:] = G.flatten()
+    odd = buf[1:].view(M, M, 2)
+    assert G.data_ptr() % 16 == 0 and odd.data_ptr() % 16 == 8
+    E = torch.linspace(-3.0, 3.0, 9, device="cuda", dtype=torch.float64)
+    args = dict(e_min=-7.0, e_max=9.0, eta=0.3, orbitals_per_nm2=30.0)
+    assert torch.equal(K.reconstruct_sigma_bastin(odd, E, **args), K.reconstruct_sigma_bastin(G, E, **args))
+    om = torch.linspace(0.3, 3.0, 5, device="cuda", dtype=torch.float64)
+    assert torch.equal(K.reconstruct_sigma_optical(odd, odd[0].contiguous(), om, 0.4, **args),
+                       K.reconstruct_sigma_optical(G, G[0].contiguous(), om, 0.4, **args))
