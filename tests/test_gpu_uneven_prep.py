@@ -77,3 +77,18 @@ def test_small_lattices_cost_little_beside_a_large_one(K):
         around.append(min(t[1:]))
     print(f"around the recursion: {around[0]:.3f} ms alone, {around[1]:.3f} ms with 2000 small lattices", flush=True)
     assert around[1] <= 4 * around[0] + 0.3
+
+
+def test_ldos_batch_beyond_2_32_elements(K):
+    """Five lattices of 1024 x 1024 with 256 vectors: 5.4e9 numbers to clear, more than one
+    launch has threads; each lattice alone has fewer."""
+    lat = wl.Lattice(kind=wl.HONEYCOMB, L1=1024, L2=1024, t=-2.7, anderson_w=0.5, e_min=-9.0, e_max=9.0)
+    lats = [lat.replace(disorder_seed=i) for i in range(5)]
+    sites = [int(s) for s in np.random.default_rng(2).integers(0, lat.n_orbitals, 256)]
+    par = wl.DosParams(num_moments=4, precision=wl.FP32, start=wl.START_SITES, sites=sites)
+    K.release_workspace()
+    mu, _ = K.moments_dos(lats, par)
+    for i in (0, 4):
+        one, _ = K.moments_dos([lats[i]], par)
+        assert np.max(np.abs(mu[i] - one[0])) <= 1e-12
+    K.release_workspace()
