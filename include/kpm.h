@@ -201,8 +201,7 @@ int kpm_moments_dos_noalloc(const kpm_lattice_t* lat, int32_t n_lat, const kpm_d
  * Launch-shape autotuner (the analogue of the paper's user-tuned TILE size,
  * Sec. 3(b) and Table 1).  Runs the recursion for probe_steps steps with each
  * candidate (kernel variant 1..6 x block x rows x grid x chunks, and the shape that
- * the library chooses by itself: patches, or rows of fewer than 2048 tiles) on the
- * given workload, timed with hipEvents on hip_stream, re-times the three fastest on
+ * the library chooses by itself) on the given workload, timed with hipEvents on hip_stream, re-times the three fastest on
  * 4 probe_steps steps (median of three rounds), and returns the one with the
  * shortest time per step in *best (and its algorithmic GB/s in *best_gbs, may
  * be NULL; the sweep variants move fewer bytes per step, so GB/s does not rank
