@@ -1725,6 +1725,9 @@ static int plan_run(kpm_plan* P, double* mu_pv, double* mu_mean, int32_t on_dev,
   KPM_CHECK_ARG(P != nullptr, "plan is NULL");
   hipStream_t s = (hipStream_t)stream;
   const bool timed = P->ev[0] != nullptr;
+  // A run that failed before its wait may have work in flight on a stream of its own.
+  P->lost = P->lost || P->waiting;
+  P->waiting = true;
   P->idle = false;
   if (timed) KPM_TRY_HIP(hipEventRecord(P->ev[0], s));
   KPM_TRY_HIP(plan_launch_prep(P, s));
@@ -1772,7 +1775,8 @@ static int plan_run(kpm_plan* P, double* mu_pv, double* mu_mean, int32_t on_dev,
                                hipMemcpyDeviceToHost, s));
   // Wait also after a failure: the copies write this frame's host memory.
   const hipError_t se = ::kpm::after_call(hipStreamSynchronize(s));
-  P->idle = se == hipSuccess;
+  P->waiting = se != hipSuccess;
+  P->idle = se == hipSuccess && !P->lost;
   if (e == hipSuccess) e = se;
   if (e != hipSuccess) {
     set_error("reading the run's status flags: %s", hipGetErrorString(e));

@@ -160,6 +160,7 @@ struct kpm_plan {
   int model_wgs = 0, model_span = 256;   // and of the model build, each of model_span sites
   bool patch = false;          // the steps run on patches (sweep of them per launch)
   bool idle = false;           // a wait has covered all work on the plan's buffers
+  bool waiting = false, lost = false;   // a run has not reached its wait; an earlier one never did
   kpm::PatchShape patch_sh;
   int64_t r_base = 0;          // global index of the plan's first random vector
   hipStream_t cap_stream = nullptr;

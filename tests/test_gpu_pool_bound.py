@@ -49,3 +49,26 @@ def test_many_small_blocks_stay_within_the_bound(K):
     with_room.run(mu_per_vector=mu)
     with_room.close()
     assert torch.equal(mu, first)
+
+
+def test_blocks_of_a_failed_run_are_not_reused(K):
+    """A run that fails before its wait may leave work on its stream, and a later run on
+    another stream waits for that one only: the plan's blocks go back to the device."""
+    import torch
+    lat = wl.Lattice(kind=wl.HONEYCOMB, L1=64, L2=64, t=-2.7, e_min=-9.0, e_max=9.0)
+    par = wl.DosParams(num_moments=16, num_random=4, vector_seed=1, precision=wl.FP64)
+    mu = torch.empty((1, 4, 16), dtype=torch.float64, device="cuda")
+    for fails in (False, True):
+        plan = K.Plan([lat], par, use_graph=False)
+        K.release_workspace()
+        if fails:
+            K.debug_inject_failure(2, 1)   # the second checked operation of the run
+            with pytest.raises(K.KPMError):
+                plan.run(mu_per_vector=mu)
+            assert K.debug_inject_failure(0) == 1
+        plan.run(mu_per_vector=mu)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            plan.run(mu_per_vector=mu)
+        torch.cuda.synchronize()
+        plan.close()
+        assert (K.release_workspace() == 0) == fails
